@@ -695,26 +695,37 @@ static int refine_check(lbm_ctx *root, int kc, const lbm_ctx *c, int kf, const l
     return LBM_OK;
 }
 
-// Advance node k one step: its own step, then per child two child steps
-// (recursively), each followed by the exchange across their interface; the
-// second exchange also fills node k's interface row toward that child.
-static int refine_advance(const lbm_refine_node *nodes, int k)
+// Advance the nodes of one depth one step: their own steps, then twice a step
+// of the next depth (recursively) and the exchange across the interfaces
+// between the two; the second exchange also fills the coarser interface rows.
+// Every node but the root has at most one child (none on its parent's side),
+// so a depth holds at most one node on either side of the root, and the two
+// sides meet only in the root, in different slots: taking them together gives
+// each lattice the same steps and exchanges in the same order.
+static int refine_advance(const lbm_refine_node *nodes, const int *level, int count)
 {
-    lbm_ctx *c = nodes[k].ctx;
-    int rc = step_once(c);
-    if (rc) return rc;
-    const size_t plane = refine_plane_floats(c->q, c->a.nx, c->a.nz);
-    const int child[2] = {nodes[k].fine_lo, nodes[k].fine_hi};
-    for (int side = 0; side < 2; ++side) {
-        if (child[side] < 0) continue;
-        lbm_ctx *f = nodes[child[side]].ctx;
-        const int dy = side ? 1 : -1, yc = side ? c->a.ny - 1 : 0, yf = side ? 0 : f->a.ny - 1;
-        float *acc = (float *)nodes[k].work_dev + (size_t)side * plane;
-        for (int sub = 0; sub < 2; ++sub) {
-            if ((rc = refine_advance(nodes, child[side]))) return rc;
-            HIPCHECK(c, launch_refine_exchange(c->a, c->st, yc, f->a, c->q, f->st, yf, dy, sub, acc, c->stream),
-                     "refine exchange");
+    lbm_ctx *root = nodes[0].ctx;
+    for (int k = 0; k < count; ++k) {
+        const int rc = step_once(nodes[level[k]].ctx);
+        if (rc) return rc;
+    }
+    RefineLink links[2];
+    int next[2], nl = 0;
+    for (int k = 0; k < count; ++k) {
+        const lbm_refine_node &p = nodes[level[k]];
+        const int child[2] = {p.fine_lo, p.fine_hi};
+        for (int side = 0; side < 2; ++side) {
+            if (child[side] < 0) continue;
+            const lbm_ctx *f = nodes[child[side]].ctx;
+            const size_t plane = refine_plane_floats(p.ctx->q, p.ctx->a.nx, p.ctx->a.nz);
+            links[nl] = {&p.ctx->a, &f->a, p.ctx->st, f->st, side, (float *)p.work_dev + (size_t)side * plane};
+            next[nl++] = child[side];
         }
+    }
+    for (int sub = 0; nl && sub < 2; ++sub) {
+        const int rc = refine_advance(nodes, next, nl);
+        if (rc) return rc;
+        HIPCHECK(root, launch_refine_exchange(links, nl, root->q, sub, root->stream), "refine exchange");
     }
     return LBM_OK;
 }
@@ -779,7 +790,8 @@ static int refine_tree_step(const lbm_refine_node *nodes, int32_t count, int64_t
         }
     }
     for (int64_t t = 0; t < n; ++t) {
-        const int rc = refine_advance(nodes, 0);
+        const int root_only[1] = {0};
+        const int rc = refine_advance(nodes, root_only, 1);
         if (rc) return rc;
     }
     return LBM_OK;

@@ -29,8 +29,8 @@
 //   - after the second fine step, slot i of X takes acc_i(X).
 // So one thread per coarse interface cell does all of it with no other
 // thread touching its cells' slots, and the exchange is two launches per
-// coarse step and fine level: k_refine_exchange after the first fine step
-// (first: acc = sum) and after the second (last: X's slot i = acc + sum).
+// coarse step: k_refine_exchange after the first fine step (first: acc = sum)
+// and after the second (last: X's slot i = acc + sum).
 // acc is [q][nz_c][nx_c] FP32; only the directions i with c_iy = -dy are used.
 //
 // Bytes per launch (FP32 storage): per coarse interface cell and crossing
@@ -41,62 +41,141 @@
 
 namespace lbm {
 
-constexpr int kRefineThreads = 256;
+// the m-th direction with c_y = +1
+template <int Q>
+__host__ __device__ constexpr int crossing_up(int m)
+{
+    for (int i = 1; i < Q; ++i)
+        if (cdir(i, 1) == 1 && m-- == 0) return i;
+    return 0;
+}
+
+// One wavefront per workgroup: an interface is a few thousand cells, so small
+// workgroups spread it over the most CUs.
+constexpr int kRefineThreads = 64;
 
 __device__ inline int wrap_int(int v, int n) { return v < 0 ? v + n : (v >= n ? v - n : v); }
 
-// the exchange after a fine step (see above): one thread per coarse interface cell (X, Z)
+// What the exchange needs of a lattice: its store and the interface row's
+// place in it (the whole argument block of a lattice is four times as long,
+// and a kernel this short notices the loads).
+struct RefineRow {
+    void *pdf;
+    uint32_t row0, sy;  // stored row of z = 0 in the interface plane, rows per stored plane
+    int nx, nz, sx;
+};
+
+// one interface: the coarse and the fine row, the sums [q][nz_c][nx_c] FP32, and
+// whether the fine lattice is above the coarse one (dy = 1)
+struct RefinePair {
+    RefineRow coarse, fine;
+    float *acc;
+    int above;
+};
+
+template <int Q>
+__device__ inline uint64_t row_index(const RefineRow &r, int i, int z, int x)
+{
+    return ((uint64_t)(r.row0 + (uint32_t)z * r.sy) * Q + (uint32_t)i) * (uint32_t)r.sx + (uint32_t)x;
+}
+
+// The exchange after a fine step (see above): one thread per coarse interface
+// cell (X, Z) and interface.  The levels form a stack, so at each depth at most
+// two interfaces exchange at the same time, one on either side of the coarsest
+// level; they go in one launch (blockIdx.z).
+//
+// Bound by latency: a launch moves little (2 MB at 256 x 128 coarse interface
+// cells), so the time is that of one thread's chain.  All slots are read
+// before the first is written: the lattices may be the same memory as far as
+// the compiler knows, and with each direction's stores before the next one's
+// loads a thread made one round trip to memory per crossing direction.
+// Measured at two interfaces of 256 x 128 coarse cells, D3Q19 FP32: 6.1 us for
+// both, against 7.8 us each before.
 template <int Q, int SC, int SF>
 __global__ void __launch_bounds__(kRefineThreads)
-    k_refine_exchange(LatticeArgs c, int yc, LatticeArgs f, int yf, int dy, int last, float *acc)
+    k_refine_exchange(RefinePair p0, RefinePair p1, int last)
 {
     using C = Store<SC>;
     using F = Store<SF>;
+    const RefinePair p = blockIdx.z ? p1 : p0;
+    const RefineRow c = p.coarse, f = p.fine;
+    const bool below = !p.above;
+    float *acc = p.acc;
     typename C::T *Ac = (typename C::T *)c.pdf;
     typename F::T *Af = (typename F::T *)f.pdf;
     const int X = blockIdx.x * kRefineThreads + threadIdx.x, Z = blockIdx.y;
     if (X >= c.nx) return;
-    const Geom gc = make_geom(c, X, yc, Z);
+    constexpr int NC = Q == 19 ? 5 : 9;  // crossing directions
     const size_t plane = (size_t)c.nx * c.nz, k = (size_t)Z * c.nx + X;
-    for_dirs<1, Q>([&](auto I) {
-        constexpr int i = decltype(I)::value, j = opp(i);
-        if (cdir(i, 1) != -dy) return;
-        const uint64_t ci = pidx<Q>(c, i, gc.row, X);
-        const auto packet = F::cvt(C::ld(Ac + ci));
+    // The m-th pair of opposite directions that cross: i leads from the fine
+    // to the coarse level (c_iy = -dy), j back.  `up` has c_y = +1, so i = up
+    // for the lattice below.
+    uint64_t ci[NC], fi[NC][4];
+    float v[NC], part[NC][4], before[NC];
+    for_dirs<0, NC>([&](auto M) {
+        constexpr int m = decltype(M)::value, up = crossing_up<Q>(m);
+        const int i = below ? up : opp(up), j = below ? opp(up) : up;
+        const int cx = below ? cdir(up, 0) : -cdir(up, 0), cz = below ? cdir(up, 2) : -cdir(up, 2);
+        ci[m] = row_index<Q>(c, i, Z, X);
+        v[m] = C::ld(Ac + ci[m]);
+        before[m] = last ? acc[(size_t)i * plane + k] : 0.f;
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            const int zf = wrap_int(2 * Z + (b >> 1) - cz, f.nz), xf = wrap_int(2 * X + (b & 1) - cx, f.nx);
+            fi[m][b] = row_index<Q>(f, j, zf, xf);
+            part[m][b] = F::ld(Af + fi[m][b]);
+        }
+    });
+    for_dirs<0, NC>([&](auto M) {
+        constexpr int m = decltype(M)::value, up = crossing_up<Q>(m);
+        const int i = below ? up : opp(up);
+        const auto packet = F::cvt(v[m]);
         float s = 0.f;
 #pragma unroll
-        for (int bz = 0; bz < 2; ++bz) {
-            const int zf = wrap_int(2 * Z + bz - cdir(i, 2), f.nz);
-            const Geom g = make_geom(f, 0, yf, zf);
-#pragma unroll
-            for (int bx = 0; bx < 2; ++bx) {
-                const int xf = wrap_int(2 * X + bx - cdir(i, 0), f.nx);
-                typename F::T *p = Af + pidx<Q>(f, j, g.row, xf);
-                s += F::ld(p);
-                *p = packet;
-            }
+        for (int b = 0; b < 4; ++b) {
+            s += part[m][b];
+            Af[fi[m][b]] = packet;
         }
-        const float v = 0.125f * s;
+        const float w = 0.125f * s;
         if (last)
-            Ac[ci] = C::cvt(acc[i * plane + k] + v);
+            Ac[ci[m]] = C::cvt(before[m] + w);
         else
-            acc[i * plane + k] = v;
+            acc[(size_t)i * plane + k] = w;
     });
 }
 
-hipError_t launch_refine_exchange(const LatticeArgs &c, int sc, int yc, const LatticeArgs &f, int q, int sf, int yf,
-                                  int dy, int last, float *acc, hipStream_t s)
+static RefineRow refine_row(const LatticeArgs &a, int y)
 {
-    const dim3 grid((unsigned)((c.nx + kRefineThreads - 1) / kRefineThreads), (unsigned)c.nz, 1);
-    return dispatch(q, sf, [&](auto Q, auto SF) {
-        auto go = [&](auto SC) {
-            k_refine_exchange<Q.value, SC.value, SF.value><<<grid, kRefineThreads, 0, s>>>(c, yc, f, yf, dy, last, acc);
-            return hipGetLastError();
-        };
-        if (sc == ST_F32) return go(std::integral_constant<int, ST_F32>{});
-        if (sc == ST_F16) return go(std::integral_constant<int, ST_F16>{});
-        return go(std::integral_constant<int, ST_BF16>{});
-    });
+    return {a.pdf, (uint32_t)y, (uint32_t)a.sy, a.nx, a.nz, a.sx};
+}
+
+hipError_t launch_refine_exchange(const RefineLink *links, int count, int q, int last, hipStream_t s)
+{
+    RefinePair p[2];
+    for (int k = 0; k < count; ++k) {
+        const RefineLink &l = links[k];
+        p[k] = {refine_row(*l.coarse, l.above ? l.coarse->ny - 1 : 0), refine_row(*l.fine, l.above ? 0 : l.fine->ny - 1),
+                l.acc, l.above};
+    }
+    // one launch where both links have the same sizes and storage formats
+    const bool both = count == 2 && links[0].sc == links[1].sc && links[0].sf == links[1].sf &&
+                      p[0].coarse.nx == p[1].coarse.nx && p[0].coarse.nz == p[1].coarse.nz;
+    for (int k = 0; k < (both ? 1 : count); ++k) {
+        const dim3 grid((unsigned)((p[k].coarse.nx + kRefineThreads - 1) / kRefineThreads), (unsigned)p[k].coarse.nz,
+                        both ? 2 : 1);
+        const hipError_t e = dispatch(q, links[k].sf, [&](auto Q, auto SF) {
+            auto go = [&](auto SC) {
+                k_refine_exchange<Q.value, SC.value, SF.value>
+                    <<<grid, kRefineThreads, 0, s>>>(p[k], p[both ? 1 : k], last);
+                return hipGetLastError();
+            };
+            if (links[k].sc == ST_F32) return go(std::integral_constant<int, ST_F32>{});
+            if (links[k].sc == ST_F16) return go(std::integral_constant<int, ST_F16>{});
+            return go(std::integral_constant<int, ST_BF16>{});
+        });
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace lbm
