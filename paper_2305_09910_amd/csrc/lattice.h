@@ -764,14 +764,41 @@ __device__ inline void closure_rates(const LatticeArgs &a, [[maybe_unused]] cons
     }
 }
 
-// Stage the network's per-lane operand table in LDS (all threads of the
-// workgroup take part; the caller's barrier follows).
-__device__ inline void stage_mlp_table(const LatticeArgs &a, uint32_t *tab_lds)
-{
-    const int tid = threadIdx.y * blockDim.x + threadIdx.x;
-    const int nthr = blockDim.x * blockDim.y;
-    for (int k = tid; k < TAB_WORDS * 64; k += nthr) tab_lds[k] = a.mlp_tab[k];
-}
+// The network's per-lane operand table on its way to LDS.  fetch() starts the
+// loads (the table is 256-byte aligned: 16 bytes each), put() writes what has
+// arrived; all threads of the workgroup take part and the caller's barrier
+// follows put().  A kernel calls fetch() before and put() after it issues the
+// loads of its populations, so that the workgroup waits for both at once
+// (256x128x128 channel with the learned closure: 154 -> 143 us a step, with the
+// row addresses in scalar registers; staged before the loads, every workgroup
+// waited twice).
+struct MlpTable {
+    static constexpr int VECS = TAB_WORDS * 64 / 4, HELD = 4;
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    u32x4 v[HELD];
+    __device__ static int tid() { return threadIdx.y * blockDim.x + threadIdx.x; }
+    __device__ static int nthr() { return blockDim.x * blockDim.y; }
+    __device__ void fetch(const LatticeArgs &a)
+    {
+        const u32x4 *T = (const u32x4 *)a.mlp_tab;
+#pragma unroll
+        for (int j = 0; j < HELD; ++j) {
+            const int k = tid() + j * nthr();
+            if (k < VECS) v[j] = T[k];
+        }
+    }
+    __device__ void put(const LatticeArgs &a, uint32_t *lds)
+    {
+        u32x4 *L = (u32x4 *)lds;
+#pragma unroll
+        for (int j = 0; j < HELD; ++j) {
+            const int k = tid() + j * nthr();
+            if (k < VECS) L[k] = v[j];
+        }
+        // workgroups of fewer than VECS / HELD threads
+        for (int k = tid() + HELD * nthr(); k < VECS; k += nthr()) L[k] = ((const u32x4 *)a.mlp_tab)[k];
+    }
+};
 
 // Value a cut link returns to its own cell (deviation form).  The face's
 // parameters are picked with an unrolled compare chain (uniform values,

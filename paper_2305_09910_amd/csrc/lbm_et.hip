@@ -50,12 +50,8 @@ __global__ void __launch_bounds__(LBM_LB_THREADS, LBM_MIN_WAVES) k_stream_collid
         if (!active) return;
     }
     [[maybe_unused]] const uint32_t *tab = nullptr;
-    if constexpr (CL == CL_MLP) {
-        __shared__ uint32_t tab_lds[TAB_WORDS * 64];
-        stage_mlp_table(a, tab_lds);
-        __syncthreads();
-        tab = tab_lds;
-    }
+    [[maybe_unused]] MlpTable table;
+    if constexpr (CL == CL_MLP) table.fetch(a);
     const Geom g = make_geom(a, active ? x : 0, active ? y : 0, z);
     uint32_t m = 0;
     if constexpr (MASK) {
@@ -75,6 +71,12 @@ __global__ void __launch_bounds__(LBM_LB_THREADS, LBM_MIN_WAVES) k_stream_collid
         const uint64_t k = et_index<Q>(a, g, twist(i, odd), cdir(i, 0) < 0, cdir(i, 1) < 0, cdir(i, 2) < 0);
         d[i] = (CL != CL_MLP || active) ? S::template ld<nt>(A + k) : 0.f;
     });
+    if constexpr (CL == CL_MLP) {
+        __shared__ __align__(16) uint32_t tab_lds[TAB_WORDS * 64];
+        table.put(a, tab_lds);
+        __syncthreads();
+        tab = tab_lds;
+    }
 
     float drho;
     const Macro M = moments<Q>(a, d, drho);

@@ -40,7 +40,14 @@ namespace lbm {
 // odd step solid lanes write zero deviations into their own slots (see
 // below); bit 2
 // (SC_MASK_RUNS): mask words only in runs that touch a solid
-template <int Q, int ST, int CL, bool MASK, int COLL>
+//
+// ROW: every wavefront of the launch lies in one row of cells, so the row and
+// all that follows from it (the neighbour rows' addresses, the y and z face
+// tests) is the same for its lanes and is kept in scalar registers.  Used with
+// the learned closure, whose kernel is bound by its vector instructions; the
+// bandwidth-bound kernels lose more by the changed register budget than the
+// address arithmetic costs them.
+template <int Q, int ST, int CL, bool MASK, int COLL, bool ROW>
 __global__ void __launch_bounds__(LBM_LB_THREADS, LBM_MIN_WAVES)
     k_stream_collide(LatticeArgs a, int flags, [[maybe_unused]] HrrArgs h)
 {
@@ -49,7 +56,8 @@ __global__ void __launch_bounds__(LBM_LB_THREADS, LBM_MIN_WAVES)
     constexpr bool kUnified =
         LBM_UNIFIED == 1 || (LBM_UNIFIED == 2 && (MASK || ST == ST_F32) && CL != CL_MLP);
     const int x = blockIdx.x * blockDim.x + threadIdx.x;
-    const int y = blockIdx.y * blockDim.y + threadIdx.y;
+    int y = blockIdx.y * blockDim.y + threadIdx.y;
+    if constexpr (ROW) y = __builtin_amdgcn_readfirstlane(y);
     const int z = blockIdx.z;
     bool active = x < a.nx && y < a.ny;
     // The learned closure runs on the matrix cores across the whole
@@ -59,13 +67,8 @@ __global__ void __launch_bounds__(LBM_LB_THREADS, LBM_MIN_WAVES)
         if (!active) return;
     }
     [[maybe_unused]] const uint32_t *tab = nullptr;
-    if constexpr (CL == CL_MLP) {
-        // the per-lane operand table of the network, staged once per workgroup
-        __shared__ uint32_t tab_lds[TAB_WORDS * 64];
-        stage_mlp_table(a, tab_lds);
-        __syncthreads();
-        tab = tab_lds;
-    }
+    [[maybe_unused]] MlpTable table;
+    if constexpr (CL == CL_MLP) table.fetch(a);
     // Solid cells on the even step: their lanes load and store their own
     // slots unchanged, in the same instructions as the fluid lanes of the
     // wavefront.  No other cell touches a solid cell's slots, so this is race
@@ -84,7 +87,7 @@ __global__ void __launch_bounds__(LBM_LB_THREADS, LBM_MIN_WAVES)
     // the host sets the flag by the solid fraction.
     constexpr bool kKeepSolid = MASK && kUnified && CL != CL_MLP;
     bool keep = false;
-    const Geom g = make_geom(a, active ? x : 0, active ? y : 0, z);
+    const Geom g = make_geom(a, active ? x : 0, y < a.ny ? y : 0, z);
     uint32_t m = 0;
     if constexpr (MASK) {
         // with SC_MASK_RUNS the cell's mask word only where its run of 64
@@ -123,6 +126,13 @@ __global__ void __launch_bounds__(LBM_LB_THREADS, LBM_MIN_WAVES)
         load_plain<Q, ST, MASK>(a, g, m, odd, d);
     } else {
         load_canonical<Q, ST>(a, g, m, odd, d);
+    }
+    if constexpr (CL == CL_MLP) {
+        // the per-lane operand table of the network, staged once per workgroup
+        __shared__ __align__(16) uint32_t tab_lds[TAB_WORDS * 64];
+        table.put(a, tab_lds);
+        __syncthreads();
+        tab = tab_lds;
     }
 
     float drho;
@@ -509,7 +519,13 @@ hipError_t launch_build_mask(const LatticeArgs &a, int q, const uint8_t *flags, 
 template <int Q, int ST, int CL, bool MASK, int COLL>
 static void launch_sc(const LatticeArgs &a, const HrrArgs &h, int odd, const Launch &L, hipStream_t s)
 {
-    k_stream_collide<Q, ST, CL, MASK, COLL><<<L.grid, L.block, 0, s>>>(a, odd, h);
+    if constexpr (CL == CL_MLP) {
+        if (L.block.x % 64 == 0) {
+            k_stream_collide<Q, ST, CL, MASK, COLL, true><<<L.grid, L.block, 0, s>>>(a, odd, h);
+            return;
+        }
+    }
+    k_stream_collide<Q, ST, CL, MASK, COLL, false><<<L.grid, L.block, 0, s>>>(a, odd, h);
 }
 
 template <int Q, int ST, int COLL>

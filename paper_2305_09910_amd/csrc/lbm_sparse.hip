@@ -62,12 +62,8 @@ __global__ void __launch_bounds__(256) k_stream_collide_sparse(LatticeArgs a, Sp
         if (!active) return;
     }
     [[maybe_unused]] const uint32_t *tab = nullptr;
-    if constexpr (CL == CL_MLP) {
-        __shared__ uint32_t tab_lds[TAB_WORDS * 64];
-        stage_mlp_table(a, tab_lds);
-        __syncthreads();
-        tab = tab_lds;
-    }
+    [[maybe_unused]] MlpTable table;
+    if constexpr (CL == CL_MLP) table.fetch(a);
     const bool mem = CL != CL_MLP || active;
     typename S::T *A = (typename S::T *)a.pdf;
     // neighbour table: all q - 1 entries on the odd step (each serves one
@@ -92,6 +88,12 @@ __global__ void __launch_bounds__(256) k_stream_collide_sparse(LatticeArgs a, Sp
             d[i] = S::ld(A + (s >= NB_FACE0 ? sp_index<Q>(k, i) : sp_index<Q>(s, opp(i))));
         }
     });
+    if constexpr (CL == CL_MLP) {
+        __shared__ __align__(16) uint32_t tab_lds[TAB_WORDS * 64];
+        table.put(a, tab_lds);
+        __syncthreads();
+        tab = tab_lds;
+    }
 
     float drho;
     const Macro M = moments<Q>(a, d, drho);
