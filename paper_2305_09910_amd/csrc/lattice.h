@@ -366,6 +366,27 @@ struct Macro {
     float rho, ux, uy, uz;
 };
 
+// c_i . v with the components folded at compile time
+__device__ inline float dot_c(int i, const float (&v)[3])
+{
+    float s = 0.f;
+    bool any = false;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const int c = cdir(i, k);
+        if (!c) continue;
+        s = any ? (c > 0 ? s + v[k] : s - v[k]) : (c > 0 ? v[k] : -v[k]);
+        any = true;
+    }
+    return s;
+}
+
+// weights of the rest direction and of the directions with n + 1 nonzero components
+template <int Q>
+__device__ constexpr float w_rest() { return (float)wgt<Q>(0); }
+template <int Q>
+__device__ constexpr float w_class(int n) { return (float)wgt<Q>(n == 0 ? 1 : (n == 1 ? 7 : 19)); }
+
 template <int Q>
 __device__ inline Macro moments(const LatticeArgs &a, const float (&d)[Q], float &drho)
 {
@@ -445,12 +466,74 @@ __device__ inline void trt_rates(float tt, float magic, float &wp, float &wm)
     wm = rcp(0.5f + magic * rcp(tt - 0.5f));
 }
 
+// TRT with Guo forcing.  A pair's even part takes
+//   A = -wp (dp - deq+) + kp S+ = -wp/2 (d_i + d_j) + w (cu (c . g) + b),
+//   g = 4.5 rho wp u + 9 kp F, b = wp (drho - 1.5 rho u.u) - 3 kp u.F,
+// and its odd part
+//   B = -wm (dm - deq-) + km S- = -wm/2 (d_i - d_j) + w (c . h),
+//   h = 3 rho wm u + 3 km F:
+// the equilibrium and the force meet in two vectors per cell, so that a pair
+// costs 9 to 12 instructions (the collision 147 for D3Q19; written out per
+// pair as deq and S it was 230).  Where the step is bound by its vector
+// instructions or their latency this is time: 256x128x128 with the learned
+// closure 143 -> 140 us a step, 32^3 4.6 -> 4.4 us; the large bandwidth-bound
+// lattices keep theirs.
 // keep: exchange each pair instead of colliding (solid lanes on the even
 // step, which store direction i into slot opposite(i) and so put every
 // slot's own value back; see the stream-collide kernel)
 template <int Q>
 __device__ inline void trt_collide(const LatticeArgs &a, float (&d)[Q], float drho, const Macro &M, float wp,
-                                   float wm, bool keep = false)
+                                   float wm, bool keep)
+{
+    const float F[3] = {a.F[0], a.F[1], a.F[2]};
+    const float U[3] = {M.ux, M.uy, M.uz};
+    const float usq = U[0] * U[0] + U[1] * U[1] + U[2] * U[2];
+    const float uF = U[0] * F[0] + U[1] * F[1] + U[2] * F[2];
+    const float kp = 1.f - 0.5f * wp, km = 1.f - 0.5f * wm;
+    const float b = wp * (drho - 1.5f * M.rho * usq) - 3.f * kp * uF;
+    {
+        const float v = d[0] + (w_rest<Q>() * b - wp * d[0]);
+        d[0] = keep ? d[0] : v;
+    }
+    // per weight class (axis, edge and corner directions): w g, w h, w b
+    constexpr int NW = Q == 19 ? 2 : 3;
+    float g[NW][3], h[NW][3], bw[NW];
+    const float gu = 4.5f * M.rho * wp, gf = 9.f * kp, hu = 3.f * M.rho * wm, hf = 3.f * km;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const float gk = gu * U[k] + gf * F[k], hk = hu * U[k] + hf * F[k];
+#pragma unroll
+        for (int n = 0; n < NW; ++n) {
+            g[n][k] = w_class<Q>(n) * gk;
+            h[n][k] = w_class<Q>(n) * hk;
+        }
+    }
+#pragma unroll
+    for (int n = 0; n < NW; ++n) bw[n] = w_class<Q>(n) * b;
+    const float ap = -0.5f * wp, am = -0.5f * wm;
+#pragma unroll
+    for (int i = 1; i < Q; i += 2) {
+        const int n = norm1(i) - 1;
+        const float cu = dot_c(i, U), cg = dot_c(i, g[n]), ch = dot_c(i, h[n]);
+        const float di = d[i], dj = d[i + 1];
+        const float A = fmaf(ap, di + dj, fmaf(cu, cg, bw[n]));
+        const float B = fmaf(am, di - dj, ch);
+        d[i] = keep ? dj : di + (A + B);
+        d[i + 1] = keep ? di : dj + (A - B);
+    }
+}
+
+// The same collision with every pair's equilibrium and source written out, for
+// 16-bit storage.  There the order of the FP32 operations shows: a result that
+// falls on the other side of a 16-bit rounding boundary moves by 2^-11 of
+// itself, shifts the roundings of its neighbours in the next step, and after
+// ten steps a run differs from one with another order of operations by as much
+// as either differs from the FP64 one (2e-4 of the velocity on the 512x256x256
+// channel).  This order is the one that stored 16-bit states were continued
+// with so far; the shorter one gained 1.6% there.
+template <int Q>
+__device__ inline void trt_collide_16bit(const LatticeArgs &a, float (&d)[Q], float drho, const Macro &M, float wp,
+                                         float wm, bool keep)
 {
     const float F0 = a.F[0], F1 = a.F[1], F2 = a.F[2];
     const float usq = M.ux * M.ux + M.uy * M.uy + M.uz * M.uz;
@@ -481,6 +564,16 @@ __device__ inline void trt_collide(const LatticeArgs &a, float (&d)[Q], float dr
         d[i] = keep ? dj : di + A + B;
         d[i + 1] = keep ? di : dj + A - B;
     }
+}
+
+template <int Q, int ST>
+__device__ inline void trt_cell(const LatticeArgs &a, float (&d)[Q], float drho, const Macro &M, float wp, float wm,
+                                bool keep = false)
+{
+    if constexpr (ST == ST_F32)
+        trt_collide<Q>(a, d, drho, M, wp, wm, keep);
+    else
+        trt_collide_16bit<Q>(a, d, drho, M, wp, wm, keep);
 }
 
 // Multiple-relaxation-time collision on deviations.  Forward transform

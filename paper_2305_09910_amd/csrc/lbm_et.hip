@@ -85,7 +85,7 @@ __global__ void __launch_bounds__(LBM_LB_THREADS, LBM_MIN_WAVES) k_stream_collid
     if constexpr (COLL == COLL_MRT)
         mrt_collide<Q>(a, d, drho, M, wp);
     else
-        trt_collide<Q>(a, d, drho, M, wp, wm);
+        trt_cell<Q, ST>(a, d, drho, M, wp, wm);
     if constexpr (CL == CL_MLP) {
         if (!active) return;
     }

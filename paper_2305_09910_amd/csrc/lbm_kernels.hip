@@ -153,7 +153,7 @@ __global__ void __launch_bounds__(LBM_LB_THREADS, LBM_MIN_WAVES)
         }
         hrr_collide<Q>(a, h.sigma, G, d, drho, M, keep);
     } else {
-        trt_collide<Q>(a, d, drho, M, wp, wm, keep);
+        trt_cell<Q, ST>(a, d, drho, M, wp, wm, keep);
     }
     if constexpr (CL == CL_MLP) {
         if (!active) return;
@@ -231,7 +231,7 @@ __global__ void __launch_bounds__(256, LBM_MIN_WAVES) k_even_pair16(LatticeArgs 
         if constexpr (COLL == COLL_MRT)
             mrt_collide<Q>(a, d[c], drho, M, wp);
         else
-            trt_collide<Q>(a, d[c], drho, M, wp, wm);
+            trt_cell<Q, ST>(a, d[c], drho, M, wp, wm);
         if (a.any_vp) {
 #pragma unroll
             for (int i = 1; i < Q; ++i) {

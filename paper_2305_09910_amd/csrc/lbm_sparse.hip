@@ -102,7 +102,7 @@ __global__ void __launch_bounds__(256) k_stream_collide_sparse(LatticeArgs a, Sp
     if constexpr (COLL == COLL_MRT)
         mrt_collide<Q>(a, d, drho, M, wp);
     else
-        trt_collide<Q>(a, d, drho, M, wp, wm);
+        trt_cell<Q, ST>(a, d, drho, M, wp, wm);
     if constexpr (CL == CL_MLP) {
         if (!active) return;
     }
