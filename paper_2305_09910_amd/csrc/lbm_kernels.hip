@@ -135,25 +135,27 @@ __global__ void __launch_bounds__(LBM_LB_THREADS, LBM_MIN_WAVES)
         tab = tab_lds;
     }
 
-    float drho;
-    const Macro M = moments<Q>(a, d, drho);
-    float wp, wm;
-    closure_rates<Q, CL>(a, tab, d, drho, M, active, wp, wm);
-    if constexpr (COLL == COLL_MRT) {
-        mrt_collide<Q>(a, d, drho, M, wp, keep);
-    } else if constexpr (COLL == COLL_HRR) {
-        // finite-difference gradient of the previous step's velocities; this
-        // step's velocities go to the other field (solid cells keep zeros)
-        float G[3][3] = {};
-        if (!keep) {
-            fd_gradient<Q>(a, h, g, m, G);
-            h.unext[cidx(a, g)] = M.ux;
-            h.unext[cells(a) + cidx(a, g)] = M.uy;
-            h.unext[2 * cells(a) + cidx(a, g)] = M.uz;
-        }
-        hrr_collide<Q>(a, h.sigma, G, d, drho, M, keep);
+    Macro M;
+    if constexpr (COLL == COLL_TRT) {
+        M = trt_cell<Q, ST, CL>(a, tab, d, active, keep);
     } else {
-        trt_cell<Q, ST>(a, d, drho, M, wp, wm, keep);
+        float drho, wp, wm;
+        M = moments<Q>(a, d, drho);
+        closure_rates<Q, CL>(a, tab, d, drho, M, active, wp, wm);
+        if constexpr (COLL == COLL_MRT) {
+            mrt_collide<Q>(a, d, drho, M, wp, keep);
+        } else {
+            // finite-difference gradient of the previous step's velocities; this
+            // step's velocities go to the other field (solid cells keep zeros)
+            float G[3][3] = {};
+            if (!keep) {
+                fd_gradient<Q>(a, h, g, m, G);
+                h.unext[cidx(a, g)] = M.ux;
+                h.unext[cells(a) + cidx(a, g)] = M.uy;
+                h.unext[2 * cells(a) + cidx(a, g)] = M.uz;
+            }
+            hrr_collide<Q>(a, h.sigma, G, d, drho, M, keep);
+        }
     }
     if constexpr (CL == CL_MLP) {
         if (!active) return;
@@ -224,14 +226,15 @@ __global__ void __launch_bounds__(256, LBM_MIN_WAVES) k_even_pair16(LatticeArgs 
     });
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
-        float drho;
-        const Macro M = moments<Q>(a, d[c], drho);
-        float wp, wm;
-        closure_rates<Q, CL>(a, nullptr, d[c], drho, M, true, wp, wm);
-        if constexpr (COLL == COLL_MRT)
+        Macro M;
+        if constexpr (COLL == COLL_TRT) {
+            M = trt_cell<Q, ST, CL>(a, nullptr, d[c], true, false);
+        } else {
+            float drho, wp, wm;
+            M = moments<Q>(a, d[c], drho);
+            closure_rates<Q, CL>(a, nullptr, d[c], drho, M, true, wp, wm);
             mrt_collide<Q>(a, d[c], drho, M, wp);
-        else
-            trt_cell<Q, ST>(a, d[c], drho, M, wp, wm);
+        }
         if (a.any_vp) {
 #pragma unroll
             for (int i = 1; i < Q; ++i) {

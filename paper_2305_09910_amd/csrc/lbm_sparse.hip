@@ -95,14 +95,15 @@ __global__ void __launch_bounds__(256) k_stream_collide_sparse(LatticeArgs a, Sp
         tab = tab_lds;
     }
 
-    float drho;
-    const Macro M = moments<Q>(a, d, drho);
-    float wp, wm;
-    closure_rates<Q, CL>(a, tab, d, drho, M, active, wp, wm);
-    if constexpr (COLL == COLL_MRT)
+    Macro M;
+    if constexpr (COLL == COLL_TRT) {
+        M = trt_cell<Q, ST, CL>(a, tab, d, active, false);
+    } else {
+        float drho, wp, wm;
+        M = moments<Q>(a, d, drho);
+        closure_rates<Q, CL>(a, tab, d, drho, M, active, wp, wm);
         mrt_collide<Q>(a, d, drho, M, wp);
-    else
-        trt_cell<Q, ST>(a, d, drho, M, wp, wm);
+    }
     if constexpr (CL == CL_MLP) {
         if (!active) return;
     }

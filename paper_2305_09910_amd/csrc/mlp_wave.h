@@ -105,6 +105,27 @@ __device__ inline float softplus_fast(float o)
     return fmaxf(o, 0.f) + l;
 }
 
+// B operands of layer 1 for the two sample blocks from each lane's own inputs
+// z: block b holds samples 32b .. 32b+31 as columns; lane l supplies inputs
+// 4(l/32) .. 4(l/32)+3 (inputs 6 and 7 are zero padding).  The inputs are
+// packed first; v_permlane32_swap exchanges the upper half of its first
+// register with the lower half of its second, which is what both blocks need:
+// (z0 z1, z4 z5) and (z2 z3, 0) give the low and the high words.
+__device__ inline void input_operands(const float (&z)[6], bf16x4 &b0, bf16x4 &b1)
+{
+    const auto lo = __builtin_amdgcn_permlane32_swap(pack2_bits(z[0], z[1]), pack2_bits(z[4], z[5]), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(pack2_bits(z[2], z[3]), 0u, false, false);
+    b0 = __builtin_bit_cast(bf16x4, (uint64_t)lo[0] | ((uint64_t)hi[0] << 32));
+    b1 = __builtin_bit_cast(bf16x4, (uint64_t)lo[1] | ((uint64_t)hi[1] << 32));
+}
+
+// Lanes l < 32: s0 of lanes l and l + 32; lanes l >= 32: s1 of lanes l - 32 and l.
+__device__ inline float sum_halves(float s0, float s1)
+{
+    const auto v = __builtin_amdgcn_permlane32_swap(__float_as_uint(s0), __float_as_uint(s1), false, false);
+    return __uint_as_float(v[0]) + __uint_as_float(v[1]);
+}
+
 // Standardised inputs of this lane and the B operands of layer 1 for the
 // two sample blocks: block b holds samples 32b .. 32b+31 as columns; lane l
 // supplies inputs 4(l/32) .. 4(l/32)+3 (inputs 6 and 7 are zero padding).
@@ -113,12 +134,7 @@ __device__ inline void layer1_operands(const float *__restrict__ P, const float 
 {
 #pragma unroll
     for (int k = 0; k < 6; ++k) z[k] = (x[k] - P[P_MU + k]) / P[P_SG + k];
-    float zp[6];
-#pragma unroll
-    for (int k = 0; k < 6; ++k) zp[k] = __shfl_xor(z[k], 32, 64);
-    const bool hi = lane >= 32;
-    b0 = hi ? pack4(zp[4], zp[5], 0.f, 0.f) : pack4(z[0], z[1], z[2], z[3]);
-    b1 = hi ? pack4(z[4], z[5], 0.f, 0.f) : pack4(zp[0], zp[1], zp[2], zp[3]);
+    input_operands(z, b0, b1);
 }
 
 // A operand of layer 1: W1[l%32][4(l/32)+t], zero for the padded inputs.
@@ -201,17 +217,18 @@ __device__ inline bf16x4 tab4(const uint32_t *T, int k, int lane)
 __device__ inline float tabf(const uint32_t *T, int k, int lane) { return __uint_as_float(T[k * 64 + lane]); }
 
 // Forward pass from the operand table (fused inference).  Returns o of this
-// lane's own sample.
-__device__ inline float mlp_forward_table(const uint32_t *T, const float (&x)[6], int lane)
+// lane's own sample; a lane outside the trusted range (its o is not used)
+// enters the network with zero inputs.
+__device__ inline float mlp_forward_table(const uint32_t *T, const float (&x)[6], bool inside, int lane)
 {
-    float z[6], zp[6];
+    float z[6];
 #pragma unroll
-    for (int k = 0; k < 6; ++k) z[k] = (x[k] - tabf(T, TAB_MU + k, lane)) * tabf(T, TAB_ISG + k, lane);
-#pragma unroll
-    for (int k = 0; k < 6; ++k) zp[k] = __shfl_xor(z[k], 32, 64);
-    const bool hi = lane >= 32;
-    const bf16x4 b0 = hi ? pack4(zp[4], zp[5], 0.f, 0.f) : pack4(z[0], z[1], z[2], z[3]);
-    const bf16x4 b1 = hi ? pack4(z[4], z[5], 0.f, 0.f) : pack4(zp[0], zp[1], zp[2], zp[3]);
+    for (int k = 0; k < 6; ++k) {
+        const float v = (x[k] - tabf(T, TAB_MU + k, lane)) * tabf(T, TAB_ISG + k, lane);
+        z[k] = inside ? v : 0.f;
+    }
+    bf16x4 b0, b1;
+    input_operands(z, b0, b1);
     const bf16x4 a1 = tab4(T, 0, lane);
     f32x16 c1;
 #pragma unroll
@@ -241,9 +258,7 @@ __device__ inline float mlp_forward_table(const uint32_t *T, const float (&x)[6]
         s0 = __builtin_amdgcn_fdot2_f32_bf16(pack2(tanh_fast(g0[2 * j]), tanh_fast(g0[2 * j + 1])), w, s0, false);
         s1 = __builtin_amdgcn_fdot2_f32_bf16(pack2(tanh_fast(g1[2 * j]), tanh_fast(g1[2 * j + 1])), w, s1, false);
     }
-    s0 += __shfl_xor(s0, 32, 64);
-    s1 += __shfl_xor(s1, 32, 64);
-    return (hi ? s1 : s0) + tabf(T, TAB_B3, lane);
+    return sum_halves(s0, s1) + tabf(T, TAB_B3, lane);
 }
 
 // Forward pass.  h1_* and h2_* receive the FP32 activations of both blocks
@@ -282,9 +297,7 @@ __device__ inline float mlp_forward_wave(const float *__restrict__ P, const floa
         s0 += w * bf16_round(h2_0[r]);
         s1 += w * bf16_round(h2_1[r]);
     }
-    s0 += __shfl_xor(s0, 32, 64);
-    s1 += __shfl_xor(s1, 32, 64);
-    return (lane >= 32 ? s1 : s0) + P[P_B3];
+    return sum_halves(s0, s1) + P[P_B3];
 }
 
 __device__ inline float mlp_forward_wave(const float *__restrict__ P, const float (&x)[6], int lane)
