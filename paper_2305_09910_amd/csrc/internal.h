@@ -94,7 +94,8 @@ struct HrrArgs {
 struct Launch {
     dim3 grid, block;
 };
-Launch lattice_launch(const LatticeArgs &a);
+// mlp: for a step kernel with the learned closure
+Launch lattice_launch(const LatticeArgs &a, bool mlp = false);
 
 // Kernel launchers (return hipError_t of the launch).
 hipError_t launch_build_mask(const LatticeArgs &a, int q, const uint8_t *flags, uint32_t *mask, hipStream_t s);

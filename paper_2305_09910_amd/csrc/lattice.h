@@ -26,18 +26,14 @@
 #ifndef LBM_BLOCK
 #define LBM_BLOCK 256
 #endif
-// Row segments of LBM_WIDE cells per workgroup when nx is a multiple of it
-// (0: never): a 512-cell row then fits one workgroup and the odd step's
+// Row segments of LBM_WIDE cells per workgroup when nx is a multiple of it:
+// a 512-cell row then fits one workgroup and the odd step's
 // shifted lines at the seam are fetched once (+2% on 512x256x256).
 #ifndef LBM_WIDE
 #define LBM_WIDE 512
 #endif
-// whole rows of up to LBM_ROW_MAX cells per workgroup (0: fixed LBM_BLOCK)
-#ifndef LBM_ROW_MAX
-#define LBM_ROW_MAX 0
-#endif
 #define LBM_MAX2(a, b) ((a) > (b) ? (a) : (b))
-#define LBM_LB_THREADS LBM_MAX2(LBM_MAX2(LBM_ROW_MAX, LBM_WIDE), LBM_BLOCK)
+#define LBM_LB_THREADS LBM_MAX2(LBM_WIDE, LBM_BLOCK)
 #ifndef LBM_NT_POLICY
 #define LBM_NT_POLICY 1
 #endif

@@ -478,33 +478,50 @@ __global__ void __launch_bounds__(256) k_copy(const f32x4 *__restrict__ src, f32
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
-Launch lattice_launch(const LatticeArgs &a)
+Launch lattice_launch(const LatticeArgs &a, bool mlp)
 {
-    // LBM_BLOCK threads: BX cells along x (a row segment) times BY rows,
-    // BX the largest power of two up to LBM_BLOCK that divides nx.  When a
-    // row fits one workgroup, the +-1 shifted accesses of the odd step stay
-    // in it; wider rows share a line at each seam between workgroups.
+    // A workgroup is BX cells along x (a row segment) times BY rows.  Three
+    // things pull at it: the +-1 shifted accesses of the odd step share a line
+    // at each seam between the workgroups of a row, which different XCDs then
+    // fetch twice; lanes past the end of the row idle; and workgroups of six or
+    // more wavefronts leave fewer of them resident.
+    auto shape = [&](int bx, int by) {
+        Launch L;
+        L.block = dim3(bx, by, 1);
+        L.grid = dim3((a.nx + bx - 1) / bx, (a.ny + by - 1) / by, a.nz);
+        return L;
+    };
+    if (a.nx % LBM_WIDE == 0) return shape(LBM_WIDE, 1);
+    // Rows that 64 or 128 do not divide, measured (us per step, this choice
+    // against segments of 64 x 4 or, for multiples of 32, 32 x 8):
+    //   one workgroup per row up to 320 cells: nx = 96: 25 / 32, 130: 39 / 43,
+    //   160: 40 / 49, 246 (D3Q27, solids): 158 / 174, 300: 104 / 117 (HRR 144 / 153);
+    //   above, segments of 128 where they waste little (350, solids: 163 / 172;
+    //   a row of 384 in one workgroup 174), else the whole row again (400 in
+    //   FP16: 60 / 66, 444 with the Esoteric Twist: 114 / 122);
+    //   longer rows in segments of 256 or 320, the one with fewer idle lanes
+    //   (600: 144 / 160, 700: 101 / 109, 900: 131 / 141, 1000: 143 / 172).
+    // Not with the learned closure, bound by its vector instructions, where
+    // idle lanes and the table per workgroup cost more than seams (130: 59 us
+    // in segments, 66 in whole rows), nor for the Esoteric Twist with solids
+    // (200: 85 / 95).
+    if (a.nx > 64 && a.nx % 128 != 0 && !mlp && !(a.et && a.mask)) {
+        const int row64 = (a.nx + 63) / 64 * 64, row128 = (a.nx + 127) / 128 * 128;
+        if (a.nx > LBM_WIDE) {
+            const int w256 = (a.nx + 255) / 256 * 256, w320 = (a.nx + 319) / 320 * 320;
+            return w320 < w256 ? shape(320, 1) : shape(256, 1);
+        }
+        if (row64 == 128) return shape(128, 2);
+        if (row64 <= 320 || row64 == LBM_WIDE || row128 - a.nx > a.nx / 8) return shape(row64, 1);
+        return shape(128, 2);
+    }
+    // LBM_BLOCK threads, BX the largest power of two up to LBM_BLOCK that
+    // divides nx, else 64 with a masked tail
     int bx = LBM_BLOCK;
-    if (LBM_ROW_MAX > 0 && a.nx <= LBM_ROW_MAX && a.nx % 64 == 0) {
-        Launch L;
-        L.block = dim3(a.nx, 1, 1);
-        L.grid = dim3(1, a.ny, a.nz);
-        return L;
-    }
-    if (LBM_WIDE > 0 && a.nx % LBM_WIDE == 0) {
-        Launch L;
-        L.block = dim3(LBM_WIDE, 1, 1);
-        L.grid = dim3(a.nx / LBM_WIDE, a.ny, a.nz);
-        return L;
-    }
     while (bx > 32 && a.nx % bx != 0) bx >>= 1;
-    if (a.nx % bx != 0) bx = 64;  // ragged rows: masked tail
+    if (a.nx % bx != 0) bx = 64;
     if (bx > a.nx) bx = a.nx <= 32 ? 32 : 64;
-    const int by = LBM_BLOCK / bx;
-    Launch L;
-    L.block = dim3(bx, by, 1);
-    L.grid = dim3((a.nx + bx - 1) / bx, (a.ny + by - 1) / by, a.nz);
-    return L;
+    return shape(bx, LBM_BLOCK / bx);
 }
 
 hipError_t launch_build_mask(const LatticeArgs &a, int q, const uint8_t *flags, uint32_t *mask, hipStream_t s)
@@ -575,7 +592,7 @@ template <int Q, int ST>
 static hipError_t step_q_st(const LatticeArgs &a, const HrrArgs &h, int cl, int coll, int odd, hipStream_t s)
 {
     if (!(odd & 1) && even_pair16<Q, ST>(a, cl, coll, s)) return hipGetLastError();
-    const Launch L = lattice_launch(a);
+    const Launch L = lattice_launch(a, cl == CL_MLP);
     const bool mk = a.mask != nullptr;
     if (cl == CL_MLP) {  // the learned closure runs with the TRT collision
         if (coll != COLL_TRT) return hipErrorInvalidValue;
