@@ -451,9 +451,7 @@ __device__ inline void noneq_flux(const LatticeArgs &a, const float (&d)[Q], flo
 // closure the moments, the flux and the collision share them (moments and flux
 // about 70 instructions instead of 120 for D3Q19; 256x128x128 with the learned
 // closure 140 -> 131 us a step, together with the network's inputs packed before
-// they are exchanged).  Without a closure the separate sums are better: they need
-// fewer registers at a time (32^3 4.4 against 4.6 us, refined channel 536
-// against 559 us a coarsest step).
+// they are exchanged).
 template <int Q>
 struct Pairs {
     static constexpr int N = (Q - 1) / 2;
@@ -537,24 +535,23 @@ __device__ inline void trt_rates(float tt, float magic, float &wp, float &wm)
     wm = rcp(0.5f + magic * rcp(tt - 0.5f));
 }
 
-// TRT with Guo forcing.  A pair's even part takes
+// TRT with Guo forcing in two vectors per cell, for the closures with FP32
+// storage.  A pair's even part takes
 //   A = -wp (dp - deq+) + kp S+ = -wp/2 (d_i + d_j) + w (cu (c . g) + b),
 //   g = 4.5 rho wp u + 9 kp F, b = wp (drho - 1.5 rho u.u) - 3 kp u.F,
 // and its odd part
 //   B = -wm (dm - deq-) + km S- = -wm/2 (d_i - d_j) + w (c . h),
 //   h = 3 rho wm u + 3 km F:
-// the equilibrium and the force meet in two vectors per cell, so that a pair
-// costs 9 to 12 instructions (the collision 147 for D3Q19; written out per
-// pair as deq and S it was 230).  Where the step is bound by its vector
-// instructions or their latency this is time: 256x128x128 with the learned
-// closure 143 -> 140 us a step, 32^3 4.6 -> 4.4 us; the large bandwidth-bound
-// lattices keep theirs.
+// the equilibrium and the force meet in two vectors, so that a pair costs 9 to
+// 12 instructions (the collision 147 for D3Q19, 230 with every pair written out
+// as below).  The fused closure is bound by its vector instructions: 256x128x128
+// 143 -> 140 us a step.
 // keep: exchange each pair instead of colliding (solid lanes on the even
 // step, which store direction i into slot opposite(i) and so put every
 // slot's own value back; see the stream-collide kernel)
 template <int Q>
-__device__ inline void trt_collide(const LatticeArgs &a, float (&d)[Q], float drho, const Macro &M, float wp,
-                                   float wm, bool keep)
+__device__ inline void trt_collide_vectors(const LatticeArgs &a, float (&d)[Q], float drho, const Macro &M, float wp,
+                                           float wm, bool keep)
 {
     const float F[3] = {a.F[0], a.F[1], a.F[2]};
     const float U[3] = {M.ux, M.uy, M.uz};
@@ -594,20 +591,19 @@ __device__ inline void trt_collide(const LatticeArgs &a, float (&d)[Q], float dr
     }
 }
 
-// The same collision with every pair's equilibrium and source written out, for
-// 16-bit storage.  There the order of the FP32 operations shows: a result that
+// The same collision with every pair's equilibrium and source written out:
+// 16-bit storage, and lattices without a closure, which are bound by memory.
+// With 16-bit storage the order of the FP32 operations shows.  A result that
 // falls on the other side of a 16-bit rounding boundary moves by 2^-11 of
-// itself, shifts the roundings of its neighbours in the next step, and after
-// ten steps a run differs from one with another order of operations by as much
-// as either differs from the FP64 one (2e-4 of the velocity on the 512x256x256
-// channel).  This order is the one that stored 16-bit states were continued
-// with so far; the shorter one gained 1.6% there.
-// keep: exchange each pair instead of colliding (solid lanes on the even
-// step, which store direction i into slot opposite(i) and so put every
-// slot's own value back)
+// itself and shifts the roundings of its neighbours in the next step; after ten
+// steps two orders of operations differ by as much as either does from FP64
+// (2e-4 of the velocity on the 512x256x256 channel), and so do two 16-bit levels
+// of a refinement whose FP32 levels changed.  This order is the one that stored
+// states were continued with so far; the shorter one gained 0 to 3% there.
+// keep: as above.
 template <int Q>
-__device__ inline void trt_collide_16bit(const LatticeArgs &a, float (&d)[Q], float drho, const Macro &M, float wp,
-                                         float wm, bool keep)
+__device__ inline void trt_collide(const LatticeArgs &a, float (&d)[Q], float drho, const Macro &M, float wp, float wm,
+                                   bool keep)
 {
     const float F0 = a.F[0], F1 = a.F[1], F2 = a.F[2];
     const float usq = M.ux * M.ux + M.uy * M.uy + M.uz * M.uz;
@@ -918,8 +914,7 @@ __device__ inline void closure_rates(const LatticeArgs &a, [[maybe_unused]] cons
     }
 }
 
-// Moments, closure and TRT collision of one cell.  FP32 storage works on the
-// pairs, 16-bit storage keeps its order of operations (trt_collide_16bit).
+// Moments, closure and TRT collision of one cell.
 template <int Q, int ST, int CL>
 __device__ inline Macro trt_cell(const LatticeArgs &a, const uint32_t *tab, float (&d)[Q], bool active, bool keep)
 {
@@ -928,16 +923,12 @@ __device__ inline Macro trt_cell(const LatticeArgs &a, const uint32_t *tab, floa
         const Pairs<Q> P(d);
         const Macro M = moments<Q>(a, P, drho);
         closure_rates<Q, CL>(a, tab, P, drho, M, active, wp, wm);
-        trt_collide<Q>(a, d, drho, M, wp, wm, keep);
-        return M;
-    } else if constexpr (ST == ST_F32) {
-        const Macro M = moments<Q>(a, d, drho);
-        trt_collide<Q>(a, d, drho, M, a.omp, a.omm, keep);
+        trt_collide_vectors<Q>(a, d, drho, M, wp, wm, keep);
         return M;
     } else {
         const Macro M = moments<Q>(a, d, drho);
         closure_rates<Q, CL>(a, tab, d, drho, M, active, wp, wm);
-        trt_collide_16bit<Q>(a, d, drho, M, wp, wm, keep);
+        trt_collide<Q>(a, d, drho, M, wp, wm, keep);
         return M;
     }
 }
