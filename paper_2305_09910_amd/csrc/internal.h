@@ -94,8 +94,8 @@ struct HrrArgs {
 struct Launch {
     dim3 grid, block;
 };
-// mlp: for a step kernel with the learned closure
-Launch lattice_launch(const LatticeArgs &a, bool mlp = false);
+// launch shape of a kernel with a thread per cell (storage st); cl and coll: of a step kernel
+Launch lattice_launch(const LatticeArgs &a, int st, int cl = CL_NONE, int coll = COLL_TRT);
 
 // Kernel launchers (return hipError_t of the launch).
 hipError_t launch_build_mask(const LatticeArgs &a, int q, const uint8_t *flags, uint32_t *mask, hipStream_t s);

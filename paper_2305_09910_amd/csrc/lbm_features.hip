@@ -46,7 +46,7 @@ __global__ void __launch_bounds__(LBM_LB_THREADS) k_closure_features(LatticeArgs
 hipError_t launch_closure_features(const LatticeArgs &a, const SparseArgs &sp, int q, int st, int odd, float *x,
                                    hipStream_t s)
 {
-    const Launch L = lattice_launch(a);
+    const Launch L = lattice_launch(a, st);
     return dispatch(q, st, [&](auto Q, auto ST) {
         k_closure_features<Q.value, ST.value><<<L.grid, L.block, 0, s>>>(a, sp, odd, x);
         return hipGetLastError();

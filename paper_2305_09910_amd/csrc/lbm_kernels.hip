@@ -478,42 +478,51 @@ __global__ void __launch_bounds__(256) k_copy(const f32x4 *__restrict__ src, f32
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
-Launch lattice_launch(const LatticeArgs &a, bool mlp)
+Launch lattice_launch(const LatticeArgs &a, int st, int cl, int coll)
 {
     // A workgroup is BX cells along x (a row segment) times BY rows.  Three
-    // things pull at it: the +-1 shifted accesses of the odd step share a line
-    // at each seam between the workgroups of a row, which different XCDs then
-    // fetch twice; lanes past the end of the row idle; and workgroups of six or
-    // more wavefronts leave fewer of them resident.
+    // things pull at it: the +-1 shifted accesses of a step share a line at
+    // each seam between the workgroups of a row, which different XCDs then
+    // fetch twice; lanes past the end of the row idle; and kernels with many
+    // registers (MRT, HRR, solids) keep fewer wavefronts resident when the
+    // workgroups are large.  All figures: us per step.
     auto shape = [&](int bx, int by) {
         Launch L;
         L.block = dim3(bx, by, 1);
         L.grid = dim3((a.nx + bx - 1) / bx, (a.ny + by - 1) / by, a.nz);
         return L;
     };
-    if (a.nx % LBM_WIDE == 0) return shape(LBM_WIDE, 1);
-    // Rows that 64 or 128 do not divide, measured (us per step, this choice
-    // against segments of 64 x 4 or, for multiples of 32, 32 x 8):
-    //   one workgroup per row up to 320 cells: nx = 96: 25 / 32, 130: 39 / 43,
-    //   160: 40 / 49, 246 (D3Q27, solids): 158 / 174, 300: 104 / 117 (HRR 144 / 153);
-    //   above, segments of 128 where they waste little (350, solids: 163 / 172;
-    //   a row of 384 in one workgroup 174), else the whole row again (400 in
-    //   FP16: 60 / 66, 444 with the Esoteric Twist: 114 / 122);
-    //   longer rows in segments of 256 or 320, the one with fewer idle lanes
-    //   (600: 144 / 160, 700: 101 / 109, 900: 131 / 141, 1000: 143 / 172).
-    // Not with the learned closure, bound by its vector instructions, where
-    // idle lanes and the table per workgroup cost more than seams (130: 59 us
-    // in segments, 66 in whole rows), nor for the Esoteric Twist with solids
-    // (200: 85 / 95).
-    if (a.nx > 64 && a.nx % 128 != 0 && !mlp && !(a.et && a.mask)) {
-        const int row64 = (a.nx + 63) / 64 * 64, row128 = (a.nx + 127) / 128 * 128;
+    const bool light = coll == COLL_TRT && cl != CL_MLP && !a.mask;
+    // Rows of whole 512-cell segments: one workgroup each for the light
+    // kernels (TRT 193, 195 with 256), 256 cells for the others (512x128x128:
+    // MRT 202 / 213, HRR 255 / 264, D3Q27 with solids 360 / 371, learned
+    // closure 260 / 266).
+    if (a.nx % LBM_WIDE == 0) return shape(light || a.et ? LBM_WIDE : 256, 1);
+    // Rows that 64 or 128 do not divide.  Not with the learned closure, bound
+    // by its vector instructions, where idle lanes and the table per workgroup
+    // cost more than seams (130: 59 in segments of 64, 66 in whole rows).
+    if (a.nx > 64 && a.nx % 128 != 0 && cl != CL_MLP) {
+        const int row64 = (a.nx + 63) / 64 * 64, half = ((a.nx + 1) / 2 + 31) / 32 * 32;
+        // Longer than a workgroup: segments of 256 or 320 cells, the one with
+        // fewer idle lanes (600: 144 / 160 with 64 x 4, 900: 131 / 141, 1000: 143 / 172).
         if (a.nx > LBM_WIDE) {
             const int w256 = (a.nx + 255) / 256 * 256, w320 = (a.nx + 319) / 320 * 320;
             return w320 < w256 ? shape(320, 1) : shape(256, 1);
         }
+        // Esoteric Twist with solids: half rows, two at a time, where they waste
+        // little (D3Q27, 300: 167 / 188, 444: 276 / 285); 64 x 4 else (200: 85,
+        // 94 in whole rows).
+        const bool fits = 2 * half - a.nx <= a.nx / 8;
+        if (a.et && a.mask) return a.nx > 200 && fits ? shape(half, 2) : shape(64, 4);
+        // One workgroup per row up to 320 cells (96: 25 / 32 with 32 x 8, 130:
+        // 39 / 43 with 64 x 4, 160: 40 / 49, 246 D3Q27 with solids: 158 / 174,
+        // 300: 104 / 117, HRR 144 / 153), and above it for the Esoteric Twist
+        // (444: 102 / 110) and 16-bit storage, whose lines are 64 cells
+        // (424: 58 / 65); FP32 rows in two halves (424: 101 / 108, MRT 107 /
+        // 111, HRR 134 / 140, with solids 125 / 133).
         if (row64 == 128) return shape(128, 2);
-        if (row64 <= 320 || row64 == LBM_WIDE || row128 - a.nx > a.nx / 8) return shape(row64, 1);
-        return shape(128, 2);
+        if (row64 <= 320 || a.et || st != ST_F32) return shape(row64, 1);
+        return shape(half, 1);
     }
     // LBM_BLOCK threads, BX the largest power of two up to LBM_BLOCK that
     // divides nx, else 64 with a masked tail
@@ -526,7 +535,7 @@ Launch lattice_launch(const LatticeArgs &a, bool mlp)
 
 hipError_t launch_build_mask(const LatticeArgs &a, int q, const uint8_t *flags, uint32_t *mask, hipStream_t s)
 {
-    const Launch L = lattice_launch(a);
+    const Launch L = lattice_launch(a, ST_F32);
     if (q == 19)
         k_build_mask<19><<<L.grid, L.block, 0, s>>>(a, flags, mask);
     else
@@ -592,7 +601,7 @@ template <int Q, int ST>
 static hipError_t step_q_st(const LatticeArgs &a, const HrrArgs &h, int cl, int coll, int odd, hipStream_t s)
 {
     if (!(odd & 1) && even_pair16<Q, ST>(a, cl, coll, s)) return hipGetLastError();
-    const Launch L = lattice_launch(a, cl == CL_MLP);
+    const Launch L = lattice_launch(a, ST, cl, coll);
     const bool mk = a.mask != nullptr;
     if (cl == CL_MLP) {  // the learned closure runs with the TRT collision
         if (coll != COLL_TRT) return hipErrorInvalidValue;
@@ -626,7 +635,7 @@ hipError_t launch_step(const LatticeArgs &a, const HrrArgs &h, int q, int st, in
 hipError_t launch_init_eq(const LatticeArgs &a, const SparseArgs &sp, int q, int st, const double *rho,
                           const double *u, hipStream_t s)
 {
-    const Launch L = lattice_launch(a);
+    const Launch L = lattice_launch(a, st);
     return dispatch(q, st, [&](auto Q, auto ST) {
         k_init_eq<Q.value, ST.value><<<L.grid, L.block, 0, s>>>(a, sp, rho, u);
         return hipGetLastError();
@@ -635,7 +644,7 @@ hipError_t launch_init_eq(const LatticeArgs &a, const SparseArgs &sp, int q, int
 
 hipError_t launch_set_pdfs(const LatticeArgs &a, const SparseArgs &sp, int q, int st, const double *f, hipStream_t s)
 {
-    const Launch L = lattice_launch(a);
+    const Launch L = lattice_launch(a, st);
     return dispatch(q, st, [&](auto Q, auto ST) {
         k_set_pdfs<Q.value, ST.value><<<L.grid, L.block, 0, s>>>(a, sp, f);
         return hipGetLastError();
@@ -645,7 +654,7 @@ hipError_t launch_set_pdfs(const LatticeArgs &a, const SparseArgs &sp, int q, in
 hipError_t launch_get_pdfs(const LatticeArgs &a, const SparseArgs &sp, int q, int st, int odd, double *f,
                            hipStream_t s)
 {
-    const Launch L = lattice_launch(a);
+    const Launch L = lattice_launch(a, st);
     return dispatch(q, st, [&](auto Q, auto ST) {
         k_get_pdfs<Q.value, ST.value><<<L.grid, L.block, 0, s>>>(a, sp, odd, f);
         return hipGetLastError();
@@ -666,7 +675,7 @@ hipError_t launch_gather(const LatticeArgs &a, const SparseArgs &sp, int q, int 
 hipError_t launch_moments(const LatticeArgs &a, const SparseArgs &sp, int q, int st, int odd, float *rho, float *u,
                           hipStream_t s)
 {
-    const Launch L = lattice_launch(a);
+    const Launch L = lattice_launch(a, st);
     return dispatch(q, st, [&](auto Q, auto ST) {
         k_moments<Q.value, ST.value><<<L.grid, L.block, 0, s>>>(a, sp, odd, rho, u);
         return hipGetLastError();
