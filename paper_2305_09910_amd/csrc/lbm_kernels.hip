@@ -324,12 +324,20 @@ __global__ void __launch_bounds__(LBM_LB_THREADS) k_set_pdfs(LatticeArgs a, Spar
     }
 }
 
+// The state readers that a run calls one after the other read the lattice in
+// alternating directions: totals and closure features from the first plane to
+// the last, canonical populations and moments from the last to the first.  The
+// second of two readers then starts on what the first left in the 256 MB
+// last-level cache (320 MB state at 256x128x128: totals, moments, features and
+// populations together 440 -> 407 us, with the shorter totals); in one
+// direction each would find the cache holding the other end.  No streaming hint
+// for the same reason (moments 60 -> 69 us, populations 165 -> 179 us with it).
 template <int Q, int ST>
 __global__ void __launch_bounds__(LBM_LB_THREADS) k_get_pdfs(LatticeArgs a, SparseArgs sp, int odd, double *f)
 {
     const int x = blockIdx.x * blockDim.x + threadIdx.x;
     const int y = blockIdx.y * blockDim.y + threadIdx.y;
-    const int z = blockIdx.z;
+    const int z = a.nz - 1 - (int)blockIdx.z;
     if (x >= a.nx || y >= a.ny) return;
     const Geom g = make_geom(a, x, y, z);
     const uint32_t m = a.mask ? a.mask[cidx(a, g)] : 0u;
@@ -375,7 +383,7 @@ __global__ void __launch_bounds__(LBM_LB_THREADS) k_moments(LatticeArgs a, Spars
 {
     const int x = blockIdx.x * blockDim.x + threadIdx.x;
     const int y = blockIdx.y * blockDim.y + threadIdx.y;
-    const int z = blockIdx.z;
+    const int z = a.nz - 1 - (int)blockIdx.z;
     if (x >= a.nx || y >= a.ny) return;
     const Geom g = make_geom(a, x, y, z);
     const uint32_t m = a.mask ? a.mask[cidx(a, g)] : 0u;
@@ -396,7 +404,7 @@ __global__ void __launch_bounds__(LBM_LB_THREADS) k_moments(LatticeArgs a, Spars
 
 // Deterministic FP64 totals: each block owns a fixed slice of cells and
 // reduces it in a fixed order (lanes, then wavefronts); a second kernel sums
-// the block partials in index order.
+// the block partials in a fixed order.
 constexpr int TOT_BLOCKS = 1024;
 
 __device__ inline double wave_sum(double v)
@@ -406,20 +414,47 @@ __device__ inline double wave_sum(double v)
     return v;
 }
 
-template <int Q, int ST>
-__global__ void __launch_bounds__(256) k_totals(LatticeArgs a, SparseArgs sp, int odd, double *partial)
+// Sum of v over the workgroup's threads of one component: lanes, then
+// wavefronts in order.  red: one row of components per wavefront.
+template <int WAVES>
+__device__ inline void block_sums(const double (&acc)[5], double (*red)[5], double *out)
 {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+        const double v = wave_sum(acc[k]);
+        if (lane == 0) red[wave][k] = v;
+    }
+    __syncthreads();
+    if (threadIdx.x < 5) {
+        double v = 0.0;
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) v += red[w][threadIdx.x];
+        out[threadIdx.x] = v;
+    }
+}
+
+// Bound by memory (q populations read per cell).  WIDE: the cell index needs
+// 64 bits; below 2^32 cells it is split with 32-bit divisions, since the three
+// 64-bit ones per cell cost more than the loads could hide.  512 threads, so
+// that the 1024 blocks are the 32 wavefronts a CU holds: 256x128x128 FP32 88 us,
+// 96 with 256 threads and 64-bit divisions.
+constexpr int TOT_THREADS = 512;
+
+template <int Q, int ST, bool WIDE>
+__global__ void __launch_bounds__(TOT_THREADS) k_totals(LatticeArgs a, SparseArgs sp, int odd, double *partial)
+{
+    using I = std::conditional_t<WIDE, uint64_t, uint32_t>;
     double acc[5] = {0, 0, 0, 0, 0};
     const uint64_t n = cells(a);
     const uint64_t per_block = (n + TOT_BLOCKS - 1) / TOT_BLOCKS;
     const uint64_t lo = (uint64_t)blockIdx.x * per_block;
     const uint64_t hi = lo + per_block < n ? lo + per_block : n;
-    const uint64_t plane = (uint64_t)a.nx * (uint64_t)a.ny;
-    for (uint64_t c = lo + threadIdx.x; c < hi; c += blockDim.x) {
-        const int z = (int)(c / plane);
-        const uint64_t r = c - (uint64_t)z * plane;
-        const int y = (int)(r / (uint64_t)a.nx);
-        const int x = (int)(r - (uint64_t)y * (uint64_t)a.nx);
+    for (uint64_t c = lo + threadIdx.x; c < hi; c += TOT_THREADS) {
+        const I row = (I)c / (I)(uint32_t)a.nx;
+        const int x = (int)((I)c - row * (I)(uint32_t)a.nx);
+        const int z = (int)((uint32_t)row / (uint32_t)a.ny);
+        const int y = (int)((uint32_t)row - (uint32_t)z * (uint32_t)a.ny);
         const Geom g = make_geom(a, x, y, z);
         const uint32_t m = a.mask ? a.mask[cidx(a, g)] : 0u;
         if (m & SELF_SOLID) continue;
@@ -439,28 +474,21 @@ __global__ void __launch_bounds__(256) k_totals(LatticeArgs a, SparseArgs sp, in
         acc[3] += (double)jz;
         acc[4] += isfinite(s) ? 0.0 : 1.0;
     }
-    __shared__ double red[4][5];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-    for (int k = 0; k < 5; ++k) {
-        const double v = wave_sum(acc[k]);
-        if (lane == 0) red[wave][k] = v;
-    }
-    __syncthreads();
-    if (threadIdx.x < 5) {
-        double v = 0.0;
-        for (int w = 0; w < (int)(blockDim.x >> 6); ++w) v += red[w][threadIdx.x];
-        partial[blockIdx.x * 5 + threadIdx.x] = v;
-    }
+    __shared__ double red[TOT_THREADS / 64][5];
+    block_sums<TOT_THREADS / 64>(acc, red, partial + blockIdx.x * 5);
 }
 
-__global__ void __launch_bounds__(64) k_totals_final(const double *partial, double *out)
+// One workgroup; thread t sums the partials of blocks t, t + 256, ... (a single
+// thread per component over all of them is a chain of 1024 loads: 25 us, now 6).
+__global__ void __launch_bounds__(256) k_totals_final(const double *partial, double *out)
 {
-    const int k = threadIdx.x;
-    if (k >= 5) return;
-    double v = 0.0;
-    for (int b = 0; b < TOT_BLOCKS; ++b) v += partial[b * 5 + k];
-    out[k] = v;
+    double acc[5] = {0, 0, 0, 0, 0};
+#pragma unroll
+    for (int b = 0; b < TOT_BLOCKS / 256; ++b)
+#pragma unroll
+        for (int k = 0; k < 5; ++k) acc[k] += partial[(b * 256 + threadIdx.x) * 5 + k];
+    __shared__ double red[4][5];
+    block_sums<4>(acc, red, out);
 }
 
 // Copy: one 16-byte vector per thread, loaded and stored with the
@@ -688,11 +716,14 @@ hipError_t launch_totals(const LatticeArgs &a, const SparseArgs &sp, int q, int 
                          double *final_out, hipStream_t s)
 {
     hipError_t e = dispatch(q, st, [&](auto Q, auto ST) {
-        k_totals<Q.value, ST.value><<<TOT_BLOCKS, 256, 0, s>>>(a, sp, odd, partial);
+        if (cells(a) >> 32)
+            k_totals<Q.value, ST.value, true><<<TOT_BLOCKS, TOT_THREADS, 0, s>>>(a, sp, odd, partial);
+        else
+            k_totals<Q.value, ST.value, false><<<TOT_BLOCKS, TOT_THREADS, 0, s>>>(a, sp, odd, partial);
         return hipGetLastError();
     });
     if (e != hipSuccess) return e;
-    k_totals_final<<<1, 64, 0, s>>>(partial, final_out);
+    k_totals_final<<<1, 256, 0, s>>>(partial, final_out);
     return hipGetLastError();
 }
 
