@@ -162,6 +162,16 @@ hipError_t launch_build_sparse_table(const LatticeArgs &a, const SparseArgs &sp,
     return hipGetLastError();
 }
 
+// LDS set aside (and not used) by each workgroup of an odd step in FP32, so
+// that three of them run on a CU instead of up to eight.  The lines of one
+// direction are written by the wavefronts of several rows and by the cells whose
+// links are cut; they leave the 4 MB L2 whole only while the chunks in flight fit
+// it (32 CUs hold 10 MB of populations and table with eight workgroups each).
+// us per step on the porous medium (256^3, 70% solid): 171.4 -> 165.5 D3Q19, 270 ->
+// 263 D3Q27; 16-bit populations fit already and lose what the wavefronts hid
+// (105 -> 113).
+constexpr unsigned ODD_LDS_F32 = 52 * 1024;
+
 template <int Q, int ST, int COLL>
 static void sparse_coll(const LatticeArgs &a, const SparseArgs &sp, int cl, int odd, dim3 grid, hipStream_t s)
 {
@@ -171,10 +181,11 @@ static void sparse_coll(const LatticeArgs &a, const SparseArgs &sp, int cl, int 
             return;
         }
     }
+    const unsigned lds = odd && ST == ST_F32 ? ODD_LDS_F32 : 0;
     if (cl == CL_NONE)
-        k_stream_collide_sparse<Q, ST, CL_NONE, COLL><<<grid, 256, 0, s>>>(a, sp, odd);
+        k_stream_collide_sparse<Q, ST, CL_NONE, COLL><<<grid, 256, lds, s>>>(a, sp, odd);
     else
-        k_stream_collide_sparse<Q, ST, CL_SMAG, COLL><<<grid, 256, 0, s>>>(a, sp, odd);
+        k_stream_collide_sparse<Q, ST, CL_SMAG, COLL><<<grid, 256, lds, s>>>(a, sp, odd);
 }
 
 hipError_t launch_step_sparse(const LatticeArgs &a, const SparseArgs &sp, int q, int st, int cl, int coll, int odd,
