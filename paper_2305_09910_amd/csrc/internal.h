@@ -19,6 +19,11 @@ constexpr int SC_SOLID_ODD = 2;
 // run word of its 64 cells is nonzero (sparse solids; with dense solids
 // nearly every run is nonzero and the extra dependent load costs time)
 constexpr int SC_MASK_RUNS = 4;
+// SC_PAIRWISE: TRT with FP32 storage takes trt_collide instead of
+// trt_collide_vectors: lattices with refinement interfaces, and large ones
+// (SC_PAIRWISE_CELLS) without solids
+constexpr int SC_PAIRWISE = 8;
+constexpr uint64_t SC_PAIRWISE_CELLS = 1ull << 23;
 enum { BC_PERIODIC = 0, BC_NOSLIP = 1, BC_VELOCITY = 2, BC_PRESSURE = 3 };
 
 // Bit 31 of a cell's mask word marks the cell itself as solid; bit i
@@ -99,7 +104,7 @@ Launch lattice_launch(const LatticeArgs &a, int st, int cl = CL_NONE, int coll =
 
 // Kernel launchers (return hipError_t of the launch).
 hipError_t launch_build_mask(const LatticeArgs &a, int q, const uint8_t *flags, uint32_t *mask, hipStream_t s);
-// odd: bit 0 the step parity, optionally | SC_SOLID_ODD | SC_MASK_RUNS
+// odd: bit 0 the step parity, optionally | SC_SOLID_ODD | SC_MASK_RUNS | SC_PAIRWISE
 hipError_t launch_step(const LatticeArgs &a, const HrrArgs &h, int q, int st, int cl, int coll, int odd, hipStream_t s);
 // Esoteric Twist step (lbm_et.hip)
 hipError_t launch_step_et(const LatticeArgs &a, int q, int st, int cl, int coll, int odd, hipStream_t s);

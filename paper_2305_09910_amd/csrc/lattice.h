@@ -535,8 +535,8 @@ __device__ inline void trt_rates(float tt, float magic, float &wp, float &wm)
     wm = rcp(0.5f + magic * rcp(tt - 0.5f));
 }
 
-// TRT with Guo forcing in two vectors per cell, for the closures with FP32
-// storage.  A pair's even part takes
+// TRT with Guo forcing in two vectors per cell (FP32 storage, where SC_PAIRWISE is
+// not set).  A pair's even part takes
 //   A = -wp (dp - deq+) + kp S+ = -wp/2 (d_i + d_j) + w (cu (c . g) + b),
 //   g = 4.5 rho wp u + 9 kp F, b = wp (drho - 1.5 rho u.u) - 3 kp u.F,
 // and its odd part
@@ -544,8 +544,11 @@ __device__ inline void trt_rates(float tt, float magic, float &wp, float &wm)
 //   h = 3 rho wm u + 3 km F:
 // the equilibrium and the force meet in two vectors, so that a pair costs 9 to
 // 12 instructions (the collision 147 for D3Q19, 230 with every pair written out
-// as below).  The fused closure is bound by its vector instructions: 256x128x128
-// 143 -> 140 us a step.
+// as below).  It shows where a step is bound by its vector instructions or their
+// latency: 256x128x128 with the learned closure 143 -> 140 us a step, 32^3 4.6 ->
+// 4.5, 64^3 with Smagorinsky 8.3 -> 8.0, the 150x70x54 D3Q27 duct 35.5 -> 35.1.
+// Large lattices without solids are bound by memory and prefer the registers of
+// the other form (512x256x256: 853 us, 866 with this one).
 // keep: exchange each pair instead of colliding (solid lanes on the even
 // step, which store direction i into slot opposite(i) and so put every
 // slot's own value back; see the stream-collide kernel)
@@ -591,15 +594,16 @@ __device__ inline void trt_collide_vectors(const LatticeArgs &a, float (&d)[Q], 
     }
 }
 
-// The same collision with every pair's equilibrium and source written out:
-// 16-bit storage, and lattices without a closure, which are bound by memory.
-// With 16-bit storage the order of the FP32 operations shows.  A result that
-// falls on the other side of a 16-bit rounding boundary moves by 2^-11 of
-// itself and shifts the roundings of its neighbours in the next step; after ten
-// steps two orders of operations differ by as much as either does from FP64
-// (2e-4 of the velocity on the 512x256x256 channel), and so do two 16-bit levels
-// of a refinement whose FP32 levels changed.  This order is the one that stored
-// states were continued with so far; the shorter one gained 0 to 3% there.
+// The same collision with every pair's equilibrium and source written out, for
+// large lattices without solids, for 16-bit storage and for lattices with
+// refinement interfaces.  With 16-bit
+// storage the order of the FP32 operations shows.  A result that falls on the
+// other side of a 16-bit rounding boundary moves by 2^-11 of itself and shifts
+// the roundings of its neighbours in the next step; after ten steps two orders of
+// operations differ by as much as either does from FP64 (2e-4 of the velocity on
+// the 512x256x256 channel), and the 16-bit levels of a refinement differ so when
+// its FP32 levels change (8e-5 after five steps).  This order is the one that
+// stored states were continued with so far; the shorter one gained 0 to 2% there.
 // keep: as above.
 template <int Q>
 __device__ inline void trt_collide(const LatticeArgs &a, float (&d)[Q], float drho, const Macro &M, float wp, float wm,
@@ -914,16 +918,20 @@ __device__ inline void closure_rates(const LatticeArgs &a, [[maybe_unused]] cons
     }
 }
 
-// Moments, closure and TRT collision of one cell.
-template <int Q, int ST, int CL>
+// Moments, closure and TRT collision of one cell (PAIRWISE: SC_PAIRWISE is set).
+template <int Q, int ST, int CL, bool PAIRWISE = false>
 __device__ inline Macro trt_cell(const LatticeArgs &a, const uint32_t *tab, float (&d)[Q], bool active, bool keep)
 {
     float drho, wp, wm;
-    if constexpr (ST == ST_F32 && CL != CL_NONE) {
+    if constexpr (ST == ST_F32 && CL != CL_NONE && !PAIRWISE) {
         const Pairs<Q> P(d);
         const Macro M = moments<Q>(a, P, drho);
         closure_rates<Q, CL>(a, tab, P, drho, M, active, wp, wm);
         trt_collide_vectors<Q>(a, d, drho, M, wp, wm, keep);
+        return M;
+    } else if constexpr (ST == ST_F32 && !PAIRWISE) {
+        const Macro M = moments<Q>(a, d, drho);
+        trt_collide_vectors<Q>(a, d, drho, M, a.omp, a.omm, keep);
         return M;
     } else {
         const Macro M = moments<Q>(a, d, drho);

@@ -39,7 +39,7 @@ struct lbm_ctx {
     float *uvel[2];  // HRR velocity fields: step t reads uvel[t & 1], writes uvel[(t + 1) & 1]
     float hrr_sigma;
     int q, st, cl, coll;
-    int sc_flags;                             // SC_SOLID_ODD | SC_MASK_RUNS for masked AA domains with sparse solids
+    int sc_flags;                             // SC_SOLID_ODD | SC_MASK_RUNS for masked AA domains with sparse solids; SC_PAIRWISE
     int bc_kind[6];                           // the domain's face kinds (LBM_BC_INTERFACE kept)
     double tau_d, force_d[3], magic_d, mrt_d[5];  // the parameters as given (refinement checks)
     int64_t time;
@@ -341,6 +341,7 @@ int lbm_create(const lbm_domain *d, int stencil, const uint8_t *flags, double ta
     c->sc_flags = (c->mask && !sp && !a.et && (double)(ncell - (uint64_t)nf) <= 0.2 * (double)ncell)
                       ? SC_SOLID_ODD | SC_MASK_RUNS
                       : 0;
+    if (iface || (!c->mask && ncell >= SC_PAIRWISE_CELLS)) c->sc_flags |= SC_PAIRWISE;
     hipError_t e = hipMemsetAsync(c->fallbacks, 0, sizeof(unsigned long long), c->stream);
     if (e == hipSuccess && c->mask) {
         // stage the flags in a region that is still undefined and holds at

@@ -47,7 +47,8 @@ namespace lbm {
 // the learned closure, whose kernel is bound by its vector instructions; the
 // bandwidth-bound kernels lose more by the changed register budget than the
 // address arithmetic costs them.
-template <int Q, int ST, int CL, bool MASK, int COLL, bool ROW>
+// PAIRWISE: SC_PAIRWISE is set (TRT, FP32 storage).
+template <int Q, int ST, int CL, bool MASK, int COLL, bool ROW, bool PAIRWISE>
 __global__ void __launch_bounds__(LBM_LB_THREADS, LBM_MIN_WAVES)
     k_stream_collide(LatticeArgs a, int flags, [[maybe_unused]] HrrArgs h)
 {
@@ -137,7 +138,7 @@ __global__ void __launch_bounds__(LBM_LB_THREADS, LBM_MIN_WAVES)
 
     Macro M;
     if constexpr (COLL == COLL_TRT) {
-        M = trt_cell<Q, ST, CL>(a, tab, d, active, keep);
+        M = trt_cell<Q, ST, CL, PAIRWISE>(a, tab, d, active, keep);
     } else {
         float drho, wp, wm;
         M = moments<Q>(a, d, drho);
@@ -578,11 +579,17 @@ static void launch_sc(const LatticeArgs &a, const HrrArgs &h, int odd, const Lau
 {
     if constexpr (CL == CL_MLP) {
         if (L.block.x % 64 == 0) {
-            k_stream_collide<Q, ST, CL, MASK, COLL, true><<<L.grid, L.block, 0, s>>>(a, odd, h);
+            k_stream_collide<Q, ST, CL, MASK, COLL, true, false><<<L.grid, L.block, 0, s>>>(a, odd, h);
             return;
         }
     }
-    k_stream_collide<Q, ST, CL, MASK, COLL, false><<<L.grid, L.block, 0, s>>>(a, odd, h);
+    if constexpr (ST == ST_F32 && CL != CL_MLP && COLL == COLL_TRT) {
+        if (odd & SC_PAIRWISE) {
+            k_stream_collide<Q, ST, CL, MASK, COLL, false, true><<<L.grid, L.block, 0, s>>>(a, odd, h);
+            return;
+        }
+    }
+    k_stream_collide<Q, ST, CL, MASK, COLL, false, false><<<L.grid, L.block, 0, s>>>(a, odd, h);
 }
 
 template <int Q, int ST, int COLL>
