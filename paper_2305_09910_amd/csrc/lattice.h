@@ -260,10 +260,22 @@ __device__ inline uint64_t sp_table(uint32_t k, int j)
     return ((uint64_t)(k / SP_CHUNK) * (Q - 1) + (uint32_t)(j - 1)) * SP_CHUNK + k % SP_CHUNK;
 }
 
+// Compile-time loop over the directions (so each access can take its own
+// streaming hint).
+template <int I, int Q, class F>
+__device__ inline void for_dirs(F &&f)
+{
+    if constexpr (I < Q) {
+        f(std::integral_constant<int, I>{});
+        for_dirs<I + 1, Q>(f);
+    }
+}
+
 // ---------------------------------------------------------------------------
 // canonical read (shared by the step kernel and every state reader)
 // ---------------------------------------------------------------------------
-template <int Q, int ST>
+// STREAM: with the streaming hints of the step kernels.
+template <int Q, int ST, bool STREAM = false>
 __device__ inline void load_canonical(const LatticeArgs &a, const Geom &g, uint32_t m, int odd, float (&d)[Q])
 {
     using S = Store<ST>;
@@ -278,29 +290,20 @@ __device__ inline void load_canonical(const LatticeArgs &a, const Geom &g, uint3
         return;
     }
     if (!odd) {
-#pragma unroll
-        for (int i = 0; i < Q; ++i) d[i] = S::ld(A + pidx<Q>(a, i, g.row, g.x));
+        for_dirs<0, Q>([&](auto I) {
+            constexpr int i = decltype(I)::value;
+            d[i] = S::template ld<STREAM && Hint<i>::even>(A + pidx<Q>(a, i, g.row, g.x));
+        });
     } else {
-#pragma unroll
-        for (int i = 0; i < Q; ++i) {
+        for_dirs<0, Q>([&](auto I) {
+            constexpr int i = decltype(I)::value;
             const int dx = cdir(i, 0), dy = cdir(i, 1), dz = cdir(i, 2);
             // source x - c_i; blocked when that link is cut (mask bit of opposite(i))
             const bool cut = face_cut(g, -dx, -dy, -dz) || ((m >> opp(i)) & 1u);
             const uint64_t own = pidx<Q>(a, i, g.row, g.x);
             const uint64_t src = pidx_nbr<Q>(a, g, opp(i), -dx, -dy, -dz);
-            d[i] = S::ld(A + (cut ? own : src));
-        }
-    }
-}
-
-// Compile-time loop over the directions (so each access can take its own
-// streaming hint).
-template <int I, int Q, class F>
-__device__ inline void for_dirs(F &&f)
-{
-    if constexpr (I < Q) {
-        f(std::integral_constant<int, I>{});
-        for_dirs<I + 1, Q>(f);
+            d[i] = S::template ld<STREAM && Hint<i>::odd>(A + (cut ? own : src));
+        });
     }
 }
 
@@ -846,12 +849,12 @@ __device__ inline void hrr_collide(const LatticeArgs &a, float sigma, const floa
 // odd number of steps in slot opposite(i) of the neighbour x - c_i, or in the
 // cell's own slot i when that link is cut; solid cells read as zero
 // deviations.
-template <int Q, int ST>
+template <int Q, int ST, bool STREAM = false>
 __device__ inline void load_state(const LatticeArgs &a, const SparseArgs &sp, const Geom &g, uint32_t m, int odd,
                                   float (&d)[Q])
 {
     if (!sp.on) {
-        load_canonical<Q, ST>(a, g, m, odd, d);
+        load_canonical<Q, ST, STREAM>(a, g, m, odd, d);
         return;
     }
     using S = Store<ST>;

@@ -332,8 +332,10 @@ __global__ void __launch_bounds__(LBM_LB_THREADS) k_set_pdfs(LatticeArgs a, Spar
 // last-level cache (320 MB state at 256x128x128: totals, moments, features and
 // populations together 440 -> 407 us, with the shorter totals); in one
 // direction each would find the cache holding the other end.  No streaming hint
-// for the same reason (moments 60 -> 69 us, populations 165 -> 179 us with it).
-template <int Q, int ST>
+// on these reads for the same reason (moments 60 -> 69 us, populations 165 -> 179
+// us with it), unless the outputs alone overrun the cache (LLC_BYTES).
+// STREAM: populations written with the streaming hint.
+template <int Q, int ST, bool STREAM>
 __global__ void __launch_bounds__(LBM_LB_THREADS) k_get_pdfs(LatticeArgs a, SparseArgs sp, int odd, double *f)
 {
     const int x = blockIdx.x * blockDim.x + threadIdx.x;
@@ -350,7 +352,7 @@ __global__ void __launch_bounds__(LBM_LB_THREADS) k_get_pdfs(LatticeArgs a, Spar
         load_state<Q, ST>(a, sp, g, m, odd, d);
     }
 #pragma unroll
-    for (int i = 0; i < Q; ++i) f[(uint64_t)i * cells(a) + cidx(a, g)] = wgt<Q>(i) + (double)d[i];
+    for (int i = 0; i < Q; ++i) st_pop<STREAM>(f + (uint64_t)i * cells(a) + cidx(a, g), wgt<Q>(i) + (double)d[i]);
 }
 
 template <int Q, int ST>
@@ -379,7 +381,7 @@ __global__ void __launch_bounds__(256) k_gather(LatticeArgs a, SparseArgs sp, in
     for (int i = 0; i < Q; ++i) out[r * Q + i] = wgt<Q>(i) + (double)d[i];
 }
 
-template <int Q, int ST>
+template <int Q, int ST, bool STREAM>
 __global__ void __launch_bounds__(LBM_LB_THREADS) k_moments(LatticeArgs a, SparseArgs sp, int odd, float *rho, float *u)
 {
     const int x = blockIdx.x * blockDim.x + threadIdx.x;
@@ -388,19 +390,22 @@ __global__ void __launch_bounds__(LBM_LB_THREADS) k_moments(LatticeArgs a, Spars
     if (x >= a.nx || y >= a.ny) return;
     const Geom g = make_geom(a, x, y, z);
     const uint32_t m = a.mask ? a.mask[cidx(a, g)] : 0u;
+    auto put = [&](float r, float ux, float uy, float uz) {
+        const uint64_t n = cells(a), c = cidx(a, g);
+        st_pop<STREAM>(rho + c, r);
+        st_pop<STREAM>(u + c, ux);
+        st_pop<STREAM>(u + n + c, uy);
+        st_pop<STREAM>(u + 2 * n + c, uz);
+    };
     if (m & SELF_SOLID) {
-        rho[cidx(a, g)] = 1.f;
-        u[cidx(a, g)] = u[cells(a) + cidx(a, g)] = u[2 * cells(a) + cidx(a, g)] = 0.f;
+        put(1.f, 0.f, 0.f, 0.f);
         return;
     }
     float d[Q];
-    load_state<Q, ST>(a, sp, g, m, odd, d);
+    load_state<Q, ST, STREAM>(a, sp, g, m, odd, d);
     float drho;
     const Macro M = moments<Q>(a, d, drho);
-    rho[cidx(a, g)] = M.rho;
-    u[cidx(a, g)] = M.ux;
-    u[cells(a) + cidx(a, g)] = M.uy;
-    u[2 * cells(a) + cidx(a, g)] = M.uz;
+    put(M.rho, M.ux, M.uy, M.uz);
 }
 
 // Deterministic FP64 totals: each block owns a fixed slice of cells and
@@ -438,8 +443,9 @@ __device__ inline void block_sums(const double (&acc)[5], double (*red)[5], doub
 // Bound by memory (q populations read per cell).  WIDE: the cell index needs
 // 64 bits; below 2^32 cells it is split with 32-bit divisions, since the three
 // 64-bit ones per cell cost more than the loads could hide.  512 threads, so
-// that the 1024 blocks are the 32 wavefronts a CU holds: 256x128x128 FP32 88 us,
-// 96 with 256 threads and 64-bit divisions.
+// that the 1024 blocks are the 32 wavefronts a CU holds: 256x128x128 FP32 52 us
+// (6.1 TB/s) on a clean cache; 88 behind 256 MB of dirty lines, where 256 threads
+// and 64-bit divisions took 96.
 constexpr int TOT_THREADS = 512;
 
 template <int Q, int ST, bool WIDE>
@@ -667,6 +673,14 @@ hipError_t launch_step(const LatticeArgs &a, const HrrArgs &h, int q, int st, in
     return dispatch(q, st, [&](auto Q, auto ST) { return step_q_st<Q.value, ST.value>(a, h, cl, coll, odd, s); });
 }
 
+// Last-level cache.  Outputs that are larger are written with the streaming hint:
+// nobody finds them in the cache, and what they leave there dirty is written back
+// during the next kernel (and, with moments, their populations are then read with
+// it too).  Moments of 512x256x256 FP32 with the box filter behind them: 580 + 125
+// us, now 505 + 109; totals after the populations of 256x128x128 (637 MB) were
+// written: 88 us, now 52.
+constexpr uint64_t LLC_BYTES = 256ull << 20;
+
 hipError_t launch_init_eq(const LatticeArgs &a, const SparseArgs &sp, int q, int st, const double *rho,
                           const double *u, hipStream_t s)
 {
@@ -691,7 +705,10 @@ hipError_t launch_get_pdfs(const LatticeArgs &a, const SparseArgs &sp, int q, in
 {
     const Launch L = lattice_launch(a, st);
     return dispatch(q, st, [&](auto Q, auto ST) {
-        k_get_pdfs<Q.value, ST.value><<<L.grid, L.block, 0, s>>>(a, sp, odd, f);
+        if (cells(a) * Q.value * 8 >= LLC_BYTES)
+            k_get_pdfs<Q.value, ST.value, true><<<L.grid, L.block, 0, s>>>(a, sp, odd, f);
+        else
+            k_get_pdfs<Q.value, ST.value, false><<<L.grid, L.block, 0, s>>>(a, sp, odd, f);
         return hipGetLastError();
     });
 }
@@ -712,7 +729,10 @@ hipError_t launch_moments(const LatticeArgs &a, const SparseArgs &sp, int q, int
 {
     const Launch L = lattice_launch(a, st);
     return dispatch(q, st, [&](auto Q, auto ST) {
-        k_moments<Q.value, ST.value><<<L.grid, L.block, 0, s>>>(a, sp, odd, rho, u);
+        if (cells(a) * 16 >= LLC_BYTES)
+            k_moments<Q.value, ST.value, true><<<L.grid, L.block, 0, s>>>(a, sp, odd, rho, u);
+        else
+            k_moments<Q.value, ST.value, false><<<L.grid, L.block, 0, s>>>(a, sp, odd, rho, u);
         return hipGetLastError();
     });
 }
