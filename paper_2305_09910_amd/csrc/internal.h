@@ -24,6 +24,15 @@ constexpr int SC_MASK_RUNS = 4;
 // (SC_PAIRWISE_CELLS) without solids
 constexpr int SC_PAIRWISE = 8;
 constexpr uint64_t SC_PAIRWISE_CELLS = 1ull << 23;
+// SC_CACHED (every scheme): the lattices that step together fit the 256 MB
+// last-level cache, so the streaming hints, which keep lines out of it, are off.
+// us per step without and with hints: 32^3 4.3 / 4.5, 100^3 28.4 / 31.8 (D3Q27
+// with solids 58.3 / 59.9, learned closure 40.4 / 43.6), 128^3 47.4 / 49.3 (HRR,
+// 214 MB with its velocities: 61.8 / 66.7), 144^3 (227 MB) 71.8 / 74.4, 160^3 in
+// FP16 (155 MB) 56.4 / 60.7; beyond the cache the hints win (160^3, 311 MB: 98.3 /
+// 93.6, 200^3: 293 / 216).
+constexpr int SC_CACHED = 16;
+constexpr uint64_t CACHED_BYTES = 224ull << 20;
 enum { BC_PERIODIC = 0, BC_NOSLIP = 1, BC_VELOCITY = 2, BC_PRESSURE = 3 };
 
 // Bit 31 of a cell's mask word marks the cell itself as solid; bit i
@@ -99,17 +108,18 @@ struct HrrArgs {
 struct Launch {
     dim3 grid, block;
 };
-// launch shape of a kernel with a thread per cell (storage st); cl and coll: of a step kernel
-Launch lattice_launch(const LatticeArgs &a, int st, int cl = CL_NONE, int coll = COLL_TRT);
+// launch shape of a kernel with a thread per cell (storage st); cl, coll and
+// cached (SC_CACHED): of a step kernel
+Launch lattice_launch(const LatticeArgs &a, int st, int cl = CL_NONE, int coll = COLL_TRT, bool cached = false);
 
 // Kernel launchers (return hipError_t of the launch).
 hipError_t launch_build_mask(const LatticeArgs &a, int q, const uint8_t *flags, uint32_t *mask, hipStream_t s);
-// odd: bit 0 the step parity, optionally | SC_SOLID_ODD | SC_MASK_RUNS | SC_PAIRWISE
+// odd: bit 0 the step parity, optionally | SC_SOLID_ODD | SC_MASK_RUNS | SC_PAIRWISE | SC_CACHED
 hipError_t launch_step(const LatticeArgs &a, const HrrArgs &h, int q, int st, int cl, int coll, int odd, hipStream_t s);
-// Esoteric Twist step (lbm_et.hip)
+// Esoteric Twist step (step_et.h); odd: bit 0 the parity, optionally | SC_CACHED
 hipError_t launch_step_et(const LatticeArgs &a, int q, int st, int cl, int coll, int odd, hipStream_t s);
 // sparse addressing (lbm_sparse.hip): neighbour table from the fluid map and
-// the fluid cells' linear indices, and the step
+// the fluid cells' linear indices, and the step (odd as for the Esoteric Twist)
 hipError_t launch_build_sparse_table(const LatticeArgs &a, const SparseArgs &sp, int q, const uint32_t *fcell,
                                      uint32_t *table, hipStream_t s);
 hipError_t launch_step_sparse(const LatticeArgs &a, const SparseArgs &sp, int q, int st, int cl, int coll, int odd,

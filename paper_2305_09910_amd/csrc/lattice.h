@@ -78,10 +78,13 @@ __device__ inline void st_pop(T *p, T v)
 // cell's slots, whose lines other directions of the same rows touch again
 // (measured: 4.5% faster odd steps on the 384^3 D3Q27 obstacle flow; the
 // Esoteric Twist kernel measured slower that way and keeps its hints).
-template <int I, bool MASK = false>
+// HINT: off for lattices that fit the last-level cache (CACHED_BYTES): their lines
+// should stay there from step to step.
+template <int I, bool MASK = false, bool HINT = true>
 struct Hint {
-    static constexpr bool even = LBM_NT_POLICY != 0;
-    static constexpr bool odd = LBM_NT_POLICY == 2 || (LBM_NT_POLICY == 1 && !MASK && cdir(I, 0) == 0);
+    static constexpr bool even = HINT && LBM_NT_POLICY != 0;
+    static constexpr bool odd =
+        HINT && (LBM_NT_POLICY == 2 || (LBM_NT_POLICY == 1 && !MASK && cdir(I, 0) == 0));
 };
 
 // ---------------------------------------------------------------------------
@@ -128,6 +131,18 @@ struct Store<ST_BF16> {
     __device__ static float from_bits(uint32_t b) { return __uint_as_float((b & 0xffffu) << 16); }
     __device__ static uint32_t to_bits(float v) { return f32_to_bf16_rne(v); }
 };
+
+// ---------------------------------------------------------------------------
+// workgroup order
+// ---------------------------------------------------------------------------
+// Workgroup b of n runs on XCD b mod 8.  This hands XCD x the contiguous range of
+// its share (the first n mod 8 XCDs take one more), so that neighbouring rows and
+// planes go through the same L2.  A bijection of [0, n).
+__device__ inline uint32_t xcd_range(uint32_t b, uint32_t n)
+{
+    const uint32_t q = n / 8u, r = n % 8u, x = b % 8u, slot = b / 8u;
+    return (x < r ? x * (q + 1u) : r * (q + 1u) + (x - r) * q) + slot;
+}
 
 // ---------------------------------------------------------------------------
 // cell geometry
@@ -312,7 +327,7 @@ __device__ inline void load_canonical(const LatticeArgs &a, const Geom &g, uint3
 // on the odd step, where they select the cell's own slot instead of the
 // neighbour's -- a per-direction select, not a branch, so wavefronts that
 // mix cells next to solids with open cells do not diverge.
-template <int Q, int ST, bool MASK>
+template <int Q, int ST, bool MASK, bool HINT>
 __device__ inline void load_plain(const LatticeArgs &a, const Geom &g, uint32_t m, int odd, float (&d)[Q])
 {
     using S = Store<ST>;
@@ -321,7 +336,7 @@ __device__ inline void load_plain(const LatticeArgs &a, const Geom &g, uint32_t 
         const typename S::T *R = A + pidx<Q>(a, 0, g.row, g.x);
         for_dirs<0, Q>([&](auto I) {
             constexpr int i = decltype(I)::value;
-            d[i] = S::template ld<Hint<i, MASK>::even>(R + (uint64_t)i * (uint32_t)a.sx);
+            d[i] = S::template ld<Hint<i, MASK, HINT>::even>(R + (uint64_t)i * (uint32_t)a.sx);
         });
     } else {
         for_dirs<0, Q>([&](auto I) {
@@ -330,12 +345,12 @@ __device__ inline void load_plain(const LatticeArgs &a, const Geom &g, uint32_t 
             if constexpr (MASK) {
                 if (i != 0 && ((m >> opp(i)) & 1u)) k = pidx<Q>(a, i, g.row, g.x);
             }
-            d[i] = S::template ld<Hint<i, MASK>::odd>(A + k);
+            d[i] = S::template ld<Hint<i, MASK, HINT>::odd>(A + k);
         });
     }
 }
 
-template <int Q, int ST, bool MASK>
+template <int Q, int ST, bool MASK, bool HINT>
 __device__ inline void store_plain(const LatticeArgs &a, const Geom &g, uint32_t m, int odd, const float (&d)[Q])
 {
     using S = Store<ST>;
@@ -344,7 +359,7 @@ __device__ inline void store_plain(const LatticeArgs &a, const Geom &g, uint32_t
         typename S::T *R = A + pidx<Q>(a, 0, g.row, g.x);
         for_dirs<0, Q>([&](auto I) {
             constexpr int i = decltype(I)::value;
-            S::template st<Hint<i, MASK>::even>(R + (uint64_t)opp(i) * (uint32_t)a.sx, d[i]);
+            S::template st<Hint<i, MASK, HINT>::even>(R + (uint64_t)opp(i) * (uint32_t)a.sx, d[i]);
         });
     } else {
         for_dirs<0, Q>([&](auto I) {
@@ -353,7 +368,7 @@ __device__ inline void store_plain(const LatticeArgs &a, const Geom &g, uint32_t
             if constexpr (MASK) {
                 if (i != 0 && ((m >> i) & 1u)) k = pidx<Q>(a, opp(i), g.row, g.x);
             }
-            S::template st<Hint<i, MASK>::odd>(A + k, d[i]);
+            S::template st<Hint<i, MASK, HINT>::odd>(A + k, d[i]);
         });
     }
 }
@@ -1014,7 +1029,7 @@ __device__ inline float wall_value(const LatticeArgs &a, int face, int i, float 
 // links cut by a face or a solid neighbour (read side) and sends cut links'
 // values to the own slot (write side); velocity and pressure faces modify
 // those values in registers.
-template <int Q, int ST, bool MASK>
+template <int Q, int ST, bool MASK, bool HINT>
 __device__ inline void load_all(const LatticeArgs &a, const Geom &g, uint32_t m, int odd, float (&d)[Q])
 {
     using S = Store<ST>;
@@ -1023,7 +1038,7 @@ __device__ inline void load_all(const LatticeArgs &a, const Geom &g, uint32_t m,
         const typename S::T *R = A + pidx<Q>(a, 0, g.row, g.x);
         for_dirs<0, Q>([&](auto I) {
             constexpr int i = decltype(I)::value;
-            d[i] = S::template ld<Hint<i, MASK>::even>(R + (uint64_t)i * (uint32_t)a.sx);
+            d[i] = S::template ld<Hint<i, MASK, HINT>::even>(R + (uint64_t)i * (uint32_t)a.sx);
         });
     } else {
         for_dirs<0, Q>([&](auto I) {
@@ -1031,12 +1046,12 @@ __device__ inline void load_all(const LatticeArgs &a, const Geom &g, uint32_t m,
             const int dx = cdir(i, 0), dy = cdir(i, 1), dz = cdir(i, 2);
             const bool cut = face_cut(g, -dx, -dy, -dz) || (MASK && ((m >> opp(i)) & 1u));
             const uint64_t k = cut ? pidx<Q>(a, i, g.row, g.x) : pidx_nbr<Q>(a, g, opp(i), -dx, -dy, -dz);
-            d[i] = S::template ld<Hint<i, MASK>::odd>(A + k);
+            d[i] = S::template ld<Hint<i, MASK, HINT>::odd>(A + k);
         });
     }
 }
 
-template <int Q, int ST, bool MASK, bool SWAP>
+template <int Q, int ST, bool MASK, bool SWAP, bool HINT>
 __device__ inline void store_all(const LatticeArgs &a, const Geom &g, uint32_t m, int odd, const float (&d)[Q],
                                  const Macro &M, bool keep)
 {
@@ -1053,7 +1068,7 @@ __device__ inline void store_all(const LatticeArgs &a, const Geom &g, uint32_t m
             // a kept (solid) lane puts every slot's own value back (the TRT
             // collision has already exchanged its pairs)
             if constexpr (MASK && SWAP) v = keep ? d[opp(i)] : v;
-            S::template st<Hint<i, MASK>::even>(R + (uint64_t)opp(i) * (uint32_t)a.sx, v);
+            S::template st<Hint<i, MASK, HINT>::even>(R + (uint64_t)opp(i) * (uint32_t)a.sx, v);
         });
     } else {
         for_dirs<0, Q>([&](auto I) {
@@ -1064,7 +1079,7 @@ __device__ inline void store_all(const LatticeArgs &a, const Geom &g, uint32_t m
             float v = d[i];
             if (a.any_vp && fcut) v = wall_value<Q>(a, deciding_face(a, g, dx, dy, dz), i, v, M);
             const uint64_t k = cut ? pidx<Q>(a, opp(i), g.row, g.x) : pidx_nbr<Q>(a, g, i, dx, dy, dz);
-            S::template st<Hint<i, MASK>::odd>(A + k, v);
+            S::template st<Hint<i, MASK, HINT>::odd>(A + k, v);
         });
     }
 }

@@ -457,13 +457,23 @@ static HrrArgs hrr_args(const lbm_ctx *c, int odd)
     return h;
 }
 
-static int step_once(lbm_ctx *c)
+// Bytes that a step of the context goes through: its state, mask and neighbour
+// table.
+static uint64_t step_bytes(const lbm_ctx *c)
 {
-    const int odd = (int)(c->time & 1);
-    hipError_t e = c->sp.on  ? launch_step_sparse(c->a, c->sp, c->q, c->st, c->cl, c->coll, odd, c->stream)
-                   : c->a.et ? launch_step_et(c->a, c->q, c->st, c->cl, c->coll, odd, c->stream)
-                             : launch_step(c->a, hrr_args(c, odd), c->q, c->st, c->cl, c->coll, odd | c->sc_flags,
-                                           c->stream);
+    uint64_t b = c->state_bytes + (c->mask && !c->sp.on ? 4 * cells(c->a) : 0);
+    if (c->sp.on) b += (uint64_t)4 * (c->q - 1) * c->sp.nf;
+    return b;
+}
+
+// together: bytes of all lattices that step in turn with this one
+static int step_once(lbm_ctx *c, uint64_t together)
+{
+    const int odd = (int)(c->time & 1), cached = together <= CACHED_BYTES ? SC_CACHED : 0;
+    hipError_t e = c->sp.on  ? launch_step_sparse(c->a, c->sp, c->q, c->st, c->cl, c->coll, odd | cached, c->stream)
+                   : c->a.et ? launch_step_et(c->a, c->q, c->st, c->cl, c->coll, odd | cached, c->stream)
+                             : launch_step(c->a, hrr_args(c, odd), c->q, c->st, c->cl, c->coll,
+                                           odd | cached | c->sc_flags, c->stream);
     if (e != hipSuccess) return hip_fail(c, e, "stream_collide launch");
     ++c->time;
     return LBM_OK;
@@ -475,8 +485,9 @@ int lbm_step(lbm_ctx *c, int64_t n)
     if (n < 0) return fail(c, LBM_EINVAL, "step count must be >= 0 (got %lld)", (long long)n);
     if (c->cl == LBM_LES_MLP && !c->mlp_ready)
         return fail(c, LBM_ESTATE, "MLP closure selected but lbm_set_closure_weights was not called");
+    const uint64_t bytes = step_bytes(c);
     for (int64_t k = 0; k < n; ++k) {
-        const int rc = step_once(c);
+        const int rc = step_once(c, bytes);
         if (rc) return rc;
     }
     return LBM_OK;
@@ -703,11 +714,11 @@ static int refine_check(lbm_ctx *root, int kc, const lbm_ctx *c, int kf, const l
 // so a depth holds at most one node on either side of the root, and the two
 // sides meet only in the root, in different slots: taking them together gives
 // each lattice the same steps and exchanges in the same order.
-static int refine_advance(const lbm_refine_node *nodes, const int *level, int count)
+static int refine_advance(const lbm_refine_node *nodes, const int *level, int count, uint64_t together)
 {
     lbm_ctx *root = nodes[0].ctx;
     for (int k = 0; k < count; ++k) {
-        const int rc = step_once(nodes[level[k]].ctx);
+        const int rc = step_once(nodes[level[k]].ctx, together);
         if (rc) return rc;
     }
     RefineLink links[2];
@@ -724,7 +735,7 @@ static int refine_advance(const lbm_refine_node *nodes, const int *level, int co
         }
     }
     for (int sub = 0; nl && sub < 2; ++sub) {
-        const int rc = refine_advance(nodes, next, nl);
+        const int rc = refine_advance(nodes, next, nl, together);
         if (rc) return rc;
         HIPCHECK(root, launch_refine_exchange(links, nl, root->q, sub, root->stream), "refine exchange");
     }
@@ -790,9 +801,11 @@ static int refine_tree_step(const lbm_refine_node *nodes, int32_t count, int64_t
                             k);
         }
     }
+    uint64_t together = 0;
+    for (int k = 0; k < count; ++k) together += step_bytes(nodes[k].ctx);
     for (int64_t t = 0; t < n; ++t) {
         const int root_only[1] = {0};
-        const int rc = refine_advance(nodes, root_only, 1);
+        const int rc = refine_advance(nodes, root_only, 1, together);
         if (rc) return rc;
     }
     return LBM_OK;

@@ -34,22 +34,16 @@ namespace lbm {
 #define LBM_SPARSE_REMAP 1
 #endif
 
-// Workgroup b runs on XCD b mod 8.  The remap hands XCD x the contiguous
-// block range of its share (the first nb mod 8 XCDs take one more block), so
-// the y and z neighbours that a wavefront gathers on the odd step, a few rows
-// further along the fluid order, are read through the same L2.  A bijection
-// of [0, nb).
+// The remap (xcd_range) takes the y and z neighbours that a wavefront gathers on
+// the odd step, a few rows further along the fluid order, through the same L2.
 __device__ inline uint32_t sparse_block(int odd)
 {
-    uint32_t b = blockIdx.x;
-    if (LBM_SPARSE_REMAP == 2 || (LBM_SPARSE_REMAP == 1 && odd)) {
-        const uint32_t nb = gridDim.x, q = nb / 8u, r = nb % 8u, x = b % 8u, slot = b / 8u;
-        b = (x < r ? x * (q + 1u) : r * (q + 1u) + (x - r) * q) + slot;
-    }
-    return b;
+    if (LBM_SPARSE_REMAP == 2 || (LBM_SPARSE_REMAP == 1 && odd)) return xcd_range(blockIdx.x, gridDim.x);
+    return blockIdx.x;
 }
 
-template <int Q, int ST, int CL, int COLL>
+// HINT off: see SC_CACHED.
+template <int Q, int ST, int CL, int COLL, bool HINT>
 __global__ void __launch_bounds__(256) k_stream_collide_sparse(LatticeArgs a, SparseArgs sp, int odd)
 {
     using S = Store<ST>;
@@ -74,7 +68,7 @@ __global__ void __launch_bounds__(256) k_stream_collide_sparse(LatticeArgs a, Sp
     const bool need = odd || a.any_vp;
     for_dirs<1, Q>([&](auto J) {
         constexpr int j = decltype(J)::value;
-        t[j] = need && mem ? __builtin_nontemporal_load(sp.nbt + sp_table<Q>(k, j)) : NB_SOLID;
+        t[j] = need && mem ? ld_pop<HINT>(sp.nbt + sp_table<Q>(k, j)) : NB_SOLID;
     });
     float d[Q];
     for_dirs<0, Q>([&](auto I) {
@@ -82,7 +76,7 @@ __global__ void __launch_bounds__(256) k_stream_collide_sparse(LatticeArgs a, Sp
         if (!mem) {
             d[i] = 0.f;
         } else if (i == 0 || !odd) {
-            d[i] = S::template ld<true>(A + sp_index<Q>(k, i));
+            d[i] = S::template ld<HINT>(A + sp_index<Q>(k, i));
         } else {
             const uint32_t s = t[opp(i)];  // neighbour x - c_i
             d[i] = S::ld(A + (s >= NB_FACE0 ? sp_index<Q>(k, i) : sp_index<Q>(s, opp(i))));
@@ -111,14 +105,14 @@ __global__ void __launch_bounds__(256) k_stream_collide_sparse(LatticeArgs a, Sp
     for_dirs<0, Q>([&](auto I) {
         constexpr int i = decltype(I)::value;
         if constexpr (i == 0) {
-            S::template st<true>(A + sp_index<Q>(k, 0), d[0]);
+            S::template st<HINT>(A + sp_index<Q>(k, 0), d[0]);
         } else {
             const uint32_t e = t[i];  // neighbour x + c_i
             float v = d[i];
             // a link through a velocity or pressure face returns the face's value
             if (a.any_vp && e >= NB_FACE0 && e != NB_SOLID) v = wall_value<Q>(a, (int)(e - NB_FACE0), i, v, M);
             if (!odd)
-                S::template st<true>(A + sp_index<Q>(k, opp(i)), v);
+                S::template st<HINT>(A + sp_index<Q>(k, opp(i)), v);
             else
                 S::st(A + (e >= NB_FACE0 ? sp_index<Q>(k, opp(i)) : sp_index<Q>(e, i)), v);
         }
@@ -172,20 +166,20 @@ hipError_t launch_build_sparse_table(const LatticeArgs &a, const SparseArgs &sp,
 // (105 -> 113).
 constexpr unsigned ODD_LDS_F32 = 52 * 1024;
 
-template <int Q, int ST, int COLL>
+template <int Q, int ST, int COLL, bool HINT>
 static void sparse_coll(const LatticeArgs &a, const SparseArgs &sp, int cl, int odd, dim3 grid, hipStream_t s)
 {
     if constexpr (COLL == COLL_TRT) {
         if (cl == CL_MLP) {  // the learned closure runs with the TRT collision
-            k_stream_collide_sparse<Q, ST, CL_MLP, COLL><<<grid, 256, 0, s>>>(a, sp, odd);
+            k_stream_collide_sparse<Q, ST, CL_MLP, COLL, HINT><<<grid, 256, 0, s>>>(a, sp, odd);
             return;
         }
     }
     const unsigned lds = odd && ST == ST_F32 ? ODD_LDS_F32 : 0;
     if (cl == CL_NONE)
-        k_stream_collide_sparse<Q, ST, CL_NONE, COLL><<<grid, 256, lds, s>>>(a, sp, odd);
+        k_stream_collide_sparse<Q, ST, CL_NONE, COLL, HINT><<<grid, 256, lds, s>>>(a, sp, odd);
     else
-        k_stream_collide_sparse<Q, ST, CL_SMAG, COLL><<<grid, 256, lds, s>>>(a, sp, odd);
+        k_stream_collide_sparse<Q, ST, CL_SMAG, COLL, HINT><<<grid, 256, lds, s>>>(a, sp, odd);
 }
 
 hipError_t launch_step_sparse(const LatticeArgs &a, const SparseArgs &sp, int q, int st, int cl, int coll, int odd,
@@ -197,10 +191,17 @@ hipError_t launch_step_sparse(const LatticeArgs &a, const SparseArgs &sp, int q,
     const dim3 grid((sp.nf + 255) / 256);
     return dispatch(q, st, [&](auto Qc, auto STc) {
         constexpr int Q = decltype(Qc)::value, ST = decltype(STc)::value;
-        if (coll == COLL_MRT)
-            sparse_coll<Q, ST, COLL_MRT>(a, sp, cl, odd, grid, s);
+        auto go = [&](auto H) {
+            constexpr bool HINT = decltype(H)::value;
+            if (coll == COLL_MRT)
+                sparse_coll<Q, ST, COLL_MRT, HINT>(a, sp, cl, odd & 1, grid, s);
+            else
+                sparse_coll<Q, ST, COLL_TRT, HINT>(a, sp, cl, odd & 1, grid, s);
+        };
+        if (odd & SC_CACHED)
+            go(std::false_type{});
         else
-            sparse_coll<Q, ST, COLL_TRT>(a, sp, cl, odd, grid, s);
+            go(std::true_type{});
         return hipGetLastError();
     });
 }
