@@ -1,5 +1,5 @@
 // internal.h -- launch interface between the C ABI (lbm_api.cpp) and the
-// HIP kernels (lbm_kernels.hip).  Not installed; not part of the ABI.
+// HIP kernels (lbm_*.hip).  Not installed; not part of the ABI.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -25,13 +25,16 @@ constexpr int SC_MASK_RUNS = 4;
 constexpr int SC_PAIRWISE = 8;
 constexpr uint64_t SC_PAIRWISE_CELLS = 1ull << 23;
 // SC_CACHED (every scheme): the lattices that step together fit the 256 MB
-// last-level cache, so the streaming hints, which keep lines out of it, are off.
+// last-level cache, so the streaming hints, which keep lines out of it, are off
+// (dense lattices: see step_without_hints).
 // us per step without and with hints: 32^3 4.3 / 4.5, 100^3 28.4 / 31.8 (D3Q27
 // with solids 58.3 / 59.9, learned closure 40.4 / 43.6), 128^3 47.4 / 49.3 (HRR,
 // 214 MB with its velocities: 61.8 / 66.7), 144^3 (227 MB) 71.8 / 74.4, 160^3 in
 // FP16 (155 MB) 56.4 / 60.7; beyond the cache the hints win (160^3, 311 MB: 98.3 /
 // 93.6, 200^3: 293 / 216).
 constexpr int SC_CACHED = 16;
+// SC_SLABS: workgroups in slabs of planes per XCD (set by the launchers, see step_in_slabs)
+constexpr int SC_SLABS = 32;
 constexpr uint64_t CACHED_BYTES = 224ull << 20;
 enum { BC_PERIODIC = 0, BC_NOSLIP = 1, BC_VELOCITY = 2, BC_PRESSURE = 3 };
 

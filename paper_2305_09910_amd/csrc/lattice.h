@@ -1,6 +1,6 @@
 // lattice.h -- device-side core shared by the stream-collide kernels of every
-// scheme (lbm_kernels.hip: AA pattern and the state kernels; lbm_et.hip:
-// Esoteric Twist; lbm_sparse.hip: AA pattern over the fluid cells only):
+// scheme (step_aa.h: AA pattern; step_et.h: Esoteric Twist; lbm_sparse.hip: AA
+// pattern over the fluid cells only; lbm_kernels.hip: the state kernels):
 // storage formats, cell geometry, population addressing, canonical reads,
 // collision operators and wall values.
 #pragma once
@@ -142,6 +142,47 @@ __device__ inline uint32_t xcd_range(uint32_t b, uint32_t n)
 {
     const uint32_t q = n / 8u, r = n % 8u, x = b % 8u, slot = b / 8u;
     return (x < r ? x * (q + 1u) : r * (q + 1u) + (x - r) * q) + slot;
+}
+
+// Block coordinates of a step kernel: the launch's own, or with `slabs` those of
+// xcd_range, which cuts the lattice into eight slabs of planes.
+__device__ inline dim3 step_block(bool slabs)
+{
+    if (!slabs) return dim3(blockIdx.x, blockIdx.y, blockIdx.z);
+    const uint32_t gx = gridDim.x, gy = gridDim.y;
+    const uint32_t t = xcd_range(blockIdx.x + gx * (blockIdx.y + gy * blockIdx.z), gx * gy * gridDim.z);
+    const uint32_t row = t / gx, z = row / gy;
+    return dim3(t - row * gx, row - z * gy, z);
+}
+
+// When a lattice that fits the last-level cache steps in slabs.  With solids (FP32):
+// the cells along their surfaces and the neighbouring rows write the same lines, in
+// one L2 that way (us per step: 150x70x54 D3Q27 35.2 -> 31.3, 132x100x100 49.9 ->
+// 41.2, D3Q27 73.2 -> 65.5; 16-bit 61.3 -> 63.5, and beyond the cache 384^3 2376 ->
+// 2648, where one XCD's wavefronts all work in one slab of memory).  Without:
+// lattices that fit the eight L2s, unless neighbouring planes meet in one anyway
+// (48^3 6.9 -> 5.8, 32^3 4.6 -> 4.3, FP16 100x68x40 10.7 -> 9.0; 64^3, whose planes
+// are 16 workgroups, 7.6 -> 7.9); with 16 bits not for rows of 128, which share no
+// lines (128x100x60 12.7 -> 13.7), nor for Esoteric Twist (51x50x155 11.5 -> 12.0).
+constexpr uint64_t L2_BYTES = 32ull << 20;
+inline bool step_in_slabs(const LatticeArgs &a, int q, int st, dim3 grid)
+{
+    if (a.mask) return st == ST_F32;
+    if (cells(a) * q * (st == ST_F32 ? 4 : 2) > L2_BYTES || grid.x * grid.y % 8 == 0) return false;
+    return st == ST_F32 || (a.nx % 128 != 0 && !a.et);
+}
+
+// Whether a lattice that fits the last-level cache steps without hints.  Always in
+// FP32 and with solids.  16-bit lattices of the size of the L2s only in slabs or where
+// even steps go in pairs of cells (FP16, without / with hints: 64x68x80 TRT 10.1 / 9.1,
+// Esoteric Twist 10.9 / 9.6; 128x100x60 TRT 12.7 / 14.7), larger ones always (150x120x130
+// 35.8 / 38.0) but for HRR (150x120x130 67.2 / 62.0).
+inline bool step_without_hints(const LatticeArgs &a, int q, int st, int cl, int coll)
+{
+    if (st == ST_F32 || a.mask) return true;
+    if (step_in_slabs(a, q, st, lattice_launch(a, st, cl, coll, true).grid)) return true;
+    if (coll == COLL_HRR) return false;
+    return cells(a) * q * 2 > L2_BYTES || (a.nx % 128 == 0 && !a.et && coll == COLL_TRT);
 }
 
 // ---------------------------------------------------------------------------

@@ -12,7 +12,9 @@ extern template hipError_t step_aa<false>(const LatticeArgs &, const HrrArgs &, 
 
 hipError_t launch_step(const LatticeArgs &a, const HrrArgs &h, int q, int st, int cl, int coll, int odd, hipStream_t s)
 {
-    return odd & SC_CACHED ? step_aa<false>(a, h, q, st, cl, coll, odd, s) : step_aa<true>(a, h, q, st, cl, coll, odd, s);
+    return (odd & SC_CACHED) && step_without_hints(a, q, st, cl, coll)
+               ? step_aa<false>(a, h, q, st, cl, coll, odd, s)
+               : step_aa<true>(a, h, q, st, cl, coll, odd, s);
 }
 
 

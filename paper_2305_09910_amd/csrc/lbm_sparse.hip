@@ -7,7 +7,7 @@
 // cache lines.  Here only fluid cells are stored.  They are numbered in row
 // order (z, y, x) and kept in chunks of 64, one wavefront each, with the q
 // direction segments of a chunk side by side ([chunk][q][64]).  The update
-// is the AA pattern of lbm_kernels.hip applied to the fluid index:
+// is the AA pattern of step_aa.h applied to the fluid index:
 //   even step: read slot i of cell k, write slot opposite(i) of cell k;
 //   odd step:  read slot opposite(i) of the neighbour x - c_i, write slot i
 //              of the neighbour x + c_i;

@@ -61,10 +61,11 @@ __global__ void __launch_bounds__(LBM_LB_THREADS, LBM_MIN_WAVES)
     const int odd = flags & 1;
     constexpr bool kUnified =
         LBM_UNIFIED == 1 || (LBM_UNIFIED == 2 && (MASK || ST == ST_F32) && CL != CL_MLP);
-    const int x = blockIdx.x * blockDim.x + threadIdx.x;
-    int y = blockIdx.y * blockDim.y + threadIdx.y;
+    const dim3 block = step_block(!HINT && (flags & SC_SLABS));
+    const int x = block.x * blockDim.x + threadIdx.x;
+    int y = block.y * blockDim.y + threadIdx.y;
     if constexpr (ROW) y = __builtin_amdgcn_readfirstlane(y);
-    const int z = blockIdx.z;
+    const int z = block.z;
     bool active = x < a.nx && y < a.ny;
     // The learned closure runs on the matrix cores across the whole
     // wavefront, so with it every lane stays to the end; otherwise lanes
@@ -261,6 +262,7 @@ __global__ void __launch_bounds__(256, LBM_MIN_WAVES) k_even_pair16(LatticeArgs 
 template <int Q, int ST, int CL, bool MASK, int COLL, bool HINT>
 static void launch_sc(const LatticeArgs &a, const HrrArgs &h, int odd, const Launch &L, hipStream_t s)
 {
+    if (!HINT && step_in_slabs(a, Q, ST, L.grid)) odd |= SC_SLABS;
     if constexpr (CL == CL_MLP) {
         if (L.block.x % 64 == 0) {
             k_stream_collide<Q, ST, CL, MASK, COLL, true, false, HINT><<<L.grid, L.block, 0, s>>>(a, odd, h);

@@ -1,7 +1,7 @@
 // step_et.h -- fused in-place stream-collide with the Esoteric Twist.
 //
 // The in-place streaming scheme the paper's LAGOON runs use (Section 5.2),
-// as an alternative to the AA pattern of lbm_kernels.hip, on the same store
+// as an alternative to the AA pattern of step_aa.h, on the same store
 // ([z][y][q][x] rows of direction segments, deviations f_i - w_i) and with
 // the same collision operators.
 //
@@ -38,12 +38,14 @@ namespace lbm {
 __device__ inline int twist(int i, int odd) { return odd ? opp(i) : i; }
 
 template <int Q, int ST, int CL, bool MASK, int COLL, bool HINT>
-__global__ void __launch_bounds__(LBM_LB_THREADS, LBM_MIN_WAVES) k_stream_collide_et(LatticeArgs a, int odd)
+__global__ void __launch_bounds__(LBM_LB_THREADS, LBM_MIN_WAVES) k_stream_collide_et(LatticeArgs a, int flags)
 {
     using S = Store<ST>;
-    const int x = blockIdx.x * blockDim.x + threadIdx.x;
-    const int y = blockIdx.y * blockDim.y + threadIdx.y;
-    const int z = blockIdx.z;
+    const int odd = flags & 1;
+    const dim3 block = step_block(!HINT && (flags & SC_SLABS));
+    const int x = block.x * blockDim.x + threadIdx.x;
+    const int y = block.y * blockDim.y + threadIdx.y;
+    const int z = block.z;
     // With the learned closure every lane stays to the end (the network runs
     // across the wavefront); otherwise lanes outside the domain or on solid
     // cells leave at once.
@@ -141,6 +143,7 @@ hipError_t step_et(const LatticeArgs &a, int q, int st, int cl, int coll, int od
     const bool mk = a.mask != nullptr;
     return dispatch(q, st, [&](auto Qc, auto STc) {
         constexpr int Q = decltype(Qc)::value, ST = decltype(STc)::value;
+        if (!HINT && step_in_slabs(a, Q, ST, L.grid)) odd |= SC_SLABS;
         if (coll == COLL_MRT)
             et_coll<Q, ST, COLL_MRT, HINT>(a, cl, mk, odd, L, s);
         else
