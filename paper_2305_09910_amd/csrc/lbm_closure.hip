@@ -177,27 +177,39 @@ hipError_t launch_mlp_forward(const float *params, const float *x, int64_t n, fl
 
 // ---------------------------------------------------------------------------
 // loss and gradient: forward + backward per 64-sample tile on the matrix
-// cores; every block owns a fixed set of tiles and writes one partial
-// gradient; a second kernel sums the partials in a fixed order.
+// cores; every block owns a fixed set of tiles and writes its partial
+// gradients; a second kernel sums the partials in a fixed order in FP64.
 //
 // Bound by the latency of one tile: a minibatch of 65 536 samples is 1024
 // tiles, one per SIMD, so what counts is the length of one wavefront's chain.
-// One block per four tiles (a tile per wavefront) up to GRAD_BLOCKS blocks,
-// which is two per CU, as many as the registers allow; beyond that the tiles
-// of a block are its wavefronts' loop.  Measured at 65 536 samples: 13.3 us,
-// against 28.7 us with 512 blocks of two tiles, LDS rows without padding
-// (every operand read 32 deep on one bank), divisions in the activations and
-// the final lane sums through LDS permutes.
+// A tile per wavefront, four to a block.  363 registers (vector and
+// accumulation) leave one wavefront per SIMD, so 256 blocks run at a time.
+// Measured at 65 536 samples: 13.1 us, against 28.7 us with 512 blocks of two
+// tiles, LDS rows without padding (every operand read 32 deep on one bank),
+// divisions in the activations and the final lane sums through LDS permutes.
+//
+// Sums within a partial are FP32, so the GRAD_PARTIALS partials are shared out
+// as finely as the minibatch allows: a partial holds ceil(tiles / GRAD_PARTIALS)
+// tiles.  With one or two tiles each, a block writes a partial per wavefront
+// or per pair of wavefronts; with more, one per block.
 // ---------------------------------------------------------------------------
-constexpr int GRAD_BLOCKS = 512;
+constexpr int GRAD_PARTIALS = 512;
 constexpr int GRAD_WORDS = MLP_NPARAM + 1;  // gradients then the loss sum
 
-size_t mlp_work_bytes(int64_t) { return (size_t)GRAD_BLOCKS * GRAD_WORDS * sizeof(float); }
+size_t mlp_work_bytes(int64_t) { return (size_t)GRAD_PARTIALS * GRAD_WORDS * sizeof(float); }
 
-static int grad_blocks(int64_t n)
+// tiles per block and partials per block (4, 2 or 1) for n samples
+struct GradSplit {
+    int64_t per_block;
+    int blocks, parts;
+};
+
+static GradSplit grad_split(int64_t n)
 {
-    const int64_t tiles = (n + 63) / 64;
-    return (int)std::min<int64_t>((tiles + 3) / 4, GRAD_BLOCKS);
+    const int64_t tiles = (n + 63) / 64, per_partial = (tiles + GRAD_PARTIALS - 1) / GRAD_PARTIALS;
+    const int parts = per_partial == 1 ? 4 : (per_partial == 2 ? 2 : 1);
+    const int64_t per_block = parts * per_partial;
+    return {per_block, (int)((tiles + per_block - 1) / per_block), parts};
 }
 
 // LDS tile [rows][64 samples] of bfloat16 bits.  A row takes 34 words instead
@@ -244,8 +256,9 @@ __device__ inline float sum32(float v)
     return v + __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(v), 0x401F));
 }
 
+template <int PARTS>
 __global__ void __launch_bounds__(256) k_mlp_loss_grad(const float *__restrict__ P, const float *__restrict__ X,
-                                                       const float *__restrict__ T, int64_t n,
+                                                       const float *__restrict__ T, int64_t n, int64_t per_block,
                                                        float *__restrict__ work)
 {
     // per-wave tiles; after its loop each wave reuses its own tile region
@@ -265,7 +278,6 @@ __global__ void __launch_bounds__(256) k_mlp_loss_grad(const float *__restrict__
     float gb3 = 0.f, loss = 0.f;
 
     const int64_t ntiles = (n + 63) / 64;
-    const int64_t per_block = (ntiles + gridDim.x - 1) / gridDim.x;
     const int64_t t_lo = (int64_t)blockIdx.x * per_block;
     const int64_t t_hi = std::min<int64_t>(ntiles, t_lo + per_block);
     for (int64_t tile = t_lo + wave; tile < t_hi; tile += 4) {  // wave-uniform trip count
@@ -336,8 +348,10 @@ __global__ void __launch_bounds__(256) k_mlp_loss_grad(const float *__restrict__
         wave_lds_sync();
     }
 
-    // reduce each wave's partial into its own tile region (fixed order)
-    float *R = reinterpret_cast<float *>(&tiles_lds[wave]);
+    // each wave's sums: a partial of its own, or to its own tile region, where
+    // the wavefronts of a partial are added in order
+    float *out = work + (size_t)blockIdx.x * PARTS * GRAD_WORDS;
+    float *R = PARTS == 4 ? out + wave * GRAD_WORDS : reinterpret_cast<float *>(&tiles_lds[wave]);
 #pragma unroll
     for (int rr = 0; rr < 16; ++rr) {
         const int row = drow(rr, lane);
@@ -360,31 +374,38 @@ __global__ void __launch_bounds__(256) k_mlp_loss_grad(const float *__restrict__
         R[P_B3] = g3;
         R[MLP_NPARAM] = ls;
     }
+    if constexpr (PARTS == 4) return;
     __syncthreads();
     const float *R0 = reinterpret_cast<const float *>(&tiles_lds[0]);
     const float *R1 = reinterpret_cast<const float *>(&tiles_lds[1]);
     const float *R2 = reinterpret_cast<const float *>(&tiles_lds[2]);
     const float *R3 = reinterpret_cast<const float *>(&tiles_lds[3]);
-    for (int k = threadIdx.x; k < GRAD_WORDS; k += blockDim.x)
-        work[(size_t)blockIdx.x * GRAD_WORDS + k] = ((R0[k] + R1[k]) + R2[k]) + R3[k];
+    for (int k = threadIdx.x; k < GRAD_WORDS; k += blockDim.x) {
+        if constexpr (PARTS == 2) {
+            out[k] = R0[k] + R1[k];
+            out[GRAD_WORDS + k] = R2[k] + R3[k];
+        } else {
+            out[k] = ((R0[k] + R1[k]) + R2[k]) + R3[k];
+        }
+    }
 }
 
-// Sum of the blocks' partials in FP64.  A workgroup takes FINAL_WORDS
+// Sum of the partials in FP64.  A workgroup takes FINAL_WORDS
 // neighbouring words and cuts the partials into FINAL_SLICES ranges, summed
-// in block order and then in range order: a fixed order for a given number of
+// in order and then in range order: a fixed order for a given number of
 // partials.  Bound by latency: one thread per word over all partials was 512
 // dependent rounds of loads, 122 us; cut sixteen ways, 4 us.
 constexpr int FINAL_WORDS = 16, FINAL_SLICES = 16;
 
 __global__ void __launch_bounds__(FINAL_WORDS *FINAL_SLICES)
-    k_mlp_grad_final(const float *__restrict__ work, int nblocks, int64_t n, float *__restrict__ grad,
+    k_mlp_grad_final(const float *__restrict__ work, int partials, int64_t n, float *__restrict__ grad,
                      float *__restrict__ loss)
 {
     __shared__ double part[FINAL_SLICES][FINAL_WORDS];
     const int w = threadIdx.x % FINAL_WORDS, slice = threadIdx.x / FINAL_WORDS;
     const int k = blockIdx.x * FINAL_WORDS + w;
-    const int per = (nblocks + FINAL_SLICES - 1) / FINAL_SLICES;
-    const int lo = slice * per, hi = min(nblocks, lo + per);
+    const int per = (partials + FINAL_SLICES - 1) / FINAL_SLICES;
+    const int lo = slice * per, hi = min(partials, lo + per);
     double s = 0.0;
     if (k < GRAD_WORDS) {
 #pragma unroll 8
@@ -404,12 +425,17 @@ __global__ void __launch_bounds__(FINAL_WORDS *FINAL_SLICES)
 hipError_t launch_mlp_loss_grad(const float *params, const float *x, const float *t, int64_t n, float *grad,
                                 float *loss, void *work, hipStream_t s)
 {
-    const int blocks = grad_blocks(n);
-    k_mlp_loss_grad<<<blocks, 256, 0, s>>>(params, x, t, n, (float *)work);
+    const GradSplit g = grad_split(n);
+    if (g.parts == 4)
+        k_mlp_loss_grad<4><<<g.blocks, 256, 0, s>>>(params, x, t, n, g.per_block, (float *)work);
+    else if (g.parts == 2)
+        k_mlp_loss_grad<2><<<g.blocks, 256, 0, s>>>(params, x, t, n, g.per_block, (float *)work);
+    else
+        k_mlp_loss_grad<1><<<g.blocks, 256, 0, s>>>(params, x, t, n, g.per_block, (float *)work);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     k_mlp_grad_final<<<(GRAD_WORDS + FINAL_WORDS - 1) / FINAL_WORDS, FINAL_WORDS * FINAL_SLICES, 0, s>>>(
-        (const float *)work, blocks, n, grad, loss);
+        (const float *)work, g.blocks * g.parts, n, grad, loss);
     return hipGetLastError();
 }
 
@@ -422,7 +448,7 @@ hipError_t launch_mlp_loss_grad(const float *params, const float *x, const float
 // call writes the partials that it sums in full, so nothing needs clearing
 // between calls.
 // ---------------------------------------------------------------------------
-constexpr size_t NOALLOC_SCRATCH_FLOATS = (size_t)GRAD_BLOCKS * GRAD_WORDS;
+constexpr size_t NOALLOC_SCRATCH_FLOATS = (size_t)GRAD_PARTIALS * GRAD_WORDS;
 static __device__ __align__(256) float scratch[NOALLOC_SCRATCH_FLOATS];
 
 size_t mlp_noalloc_scratch_bytes() { return NOALLOC_SCRATCH_FLOATS * sizeof(float); }
