@@ -436,6 +436,7 @@ __device__ inline void store_plain(const LatticeArgs &a, const Geom &g, uint32_t
 // ---------------------------------------------------------------------------
 struct Macro {
     float rho, ux, uy, uz;
+    float j[3];  // momentum rho u (with half the force)
 };
 
 __device__ inline Macro macro(const LatticeArgs &a, float s, float jx, float jy, float jz)
@@ -443,9 +444,12 @@ __device__ inline Macro macro(const LatticeArgs &a, float s, float jx, float jy,
     Macro M;
     M.rho = 1.f + s;
     const float ir = 1.f / M.rho;
-    M.ux = (jx + 0.5f * a.F[0]) * ir;
-    M.uy = (jy + 0.5f * a.F[1]) * ir;
-    M.uz = (jz + 0.5f * a.F[2]) * ir;
+    M.j[0] = jx + 0.5f * a.F[0];
+    M.j[1] = jy + 0.5f * a.F[1];
+    M.j[2] = jz + 0.5f * a.F[2];
+    M.ux = M.j[0] * ir;
+    M.uy = M.j[1] * ir;
+    M.uz = M.j[2] * ir;
     return M;
 }
 
@@ -614,17 +618,23 @@ __device__ inline void trt_rates(float tt, float magic, float &wp, float &wm)
 // TRT with Guo forcing in two vectors per cell (FP32 storage, where SC_PAIRWISE is
 // not set).  A pair's even part takes
 //   A = -wp (dp - deq+) + kp S+ = -wp/2 (d_i + d_j) + w (cu (c . g) + b),
-//   g = 4.5 rho wp u + 9 kp F, b = wp (drho - 1.5 rho u.u) - 3 kp u.F,
+//   g = 4.5 (wp j + 2 kp F), b = wp (drho - 1.5 rho u.u) - 3 kp u.F,
 // and its odd part
 //   B = -wm (dm - deq-) + km S- = -wm/2 (d_i - d_j) + w (c . h),
-//   h = 3 rho wm u + 3 km F:
+//   h = 3 (wm j + km F):
 // the equilibrium and the force meet in two vectors, so that a pair costs 9 to
-// 12 instructions (the collision 147 for D3Q19, 230 with every pair written out
-// as below).  It shows where a step is bound by its vector instructions or their
-// latency: 256x128x128 with the learned closure 143 -> 140 us a step, 32^3 4.6 ->
-// 4.5, 64^3 with Smagorinsky 8.3 -> 8.0, the 150x70x54 D3Q27 duct 35.5 -> 35.1.
-// Large lattices without solids are bound by memory and prefer the registers of
-// the other form (512x256x256: 853 us, 866 with this one).
+// 12 instructions (the collision about 150 for D3Q19, 230 with every pair written
+// out as below).  It shows where a step is bound by its vector instructions or
+// their latency (us per step, the form below / this one: 48^3 6.0 / 5.7, with
+// Smagorinsky 6.5 / 5.8, the 150x70x54 D3Q27 duct 32.1 / 31.2, porous 96^3 sparse
+// 12.7 / 12.4).  Large lattices without solids are bound by memory and keep the
+// form below.
+//
+// g and h take the momentum itself, not rho times the velocity that was divided
+// by it, and h its factor 3 apart from the rates: a rounding that is the same in
+// every cell, as that of 3 wm or 3 w, adds up over the steps.  rms error of the
+// velocity against FP64, the form below / rho times u / this one: porous medium
+// 1.63e-8 / 1.76e-8 / 1.39e-8, vortex 32^3 after 100 steps 17.9e-8 / 6.3e-8 / 6.8e-8.
 // keep: exchange each pair instead of colliding (solid lanes on the even
 // step, which store direction i into slot opposite(i) and so put every
 // slot's own value back; see the stream-collide kernel)
@@ -645,13 +655,12 @@ __device__ inline void trt_collide_vectors(const LatticeArgs &a, float (&d)[Q], 
     // per weight class (axis, edge and corner directions): w g, w h, w b
     constexpr int NW = Q == 19 ? 2 : 3;
     float g[NW][3], h[NW][3], bw[NW];
-    const float gu = 4.5f * M.rho * wp, gf = 9.f * kp, hu = 3.f * M.rho * wm, hf = 3.f * km;
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-        const float gk = gu * U[k] + gf * F[k], hk = hu * U[k] + hf * F[k];
+        const float gk = wp * M.j[k] + 2.f * kp * F[k], hk = 3.f * (wm * M.j[k] + km * F[k]);
 #pragma unroll
         for (int n = 0; n < NW; ++n) {
-            g[n][k] = w_class<Q>(n) * gk;
+            g[n][k] = 4.5f * w_class<Q>(n) * gk;
             h[n][k] = w_class<Q>(n) * hk;
         }
     }
