@@ -20,10 +20,8 @@ constexpr int SC_SOLID_ODD = 2;
 // nearly every run is nonzero and the extra dependent load costs time)
 constexpr int SC_MASK_RUNS = 4;
 // SC_PAIRWISE: TRT with FP32 storage takes trt_collide instead of
-// trt_collide_vectors: lattices with refinement interfaces, and large ones
-// (SC_PAIRWISE_CELLS) without solids
+// trt_collide_vectors: lattices with refinement interfaces
 constexpr int SC_PAIRWISE = 8;
-constexpr uint64_t SC_PAIRWISE_CELLS = 1ull << 23;
 // SC_CACHED (every scheme): the lattices that step together fit the 256 MB
 // last-level cache, so the streaming hints, which keep lines out of it, are off
 // (dense lattices: see step_without_hints).

@@ -456,6 +456,7 @@ __device__ inline Macro macro(const LatticeArgs &a, float s, float jx, float jy,
 // c_i . v with the components folded at compile time
 __device__ inline float dot_c(int i, const float (&v)[3])
 {
+#pragma clang fp contract(off)
     float s = 0.f;
     bool any = false;
 #pragma unroll
@@ -627,14 +628,20 @@ __device__ inline void trt_rates(float tt, float magic, float &wp, float &wm)
 // out as below).  It shows where a step is bound by its vector instructions or
 // their latency (us per step, the form below / this one: 48^3 6.0 / 5.7, with
 // Smagorinsky 6.5 / 5.8, the 150x70x54 D3Q27 duct 32.1 / 31.2, porous 96^3 sparse
-// 12.7 / 12.4).  Large lattices without solids are bound by memory and keep the
-// form below.
+// 12.7 / 12.4); large lattices are bound by memory and take either (256^3 438 /
+// 436, D3Q27 649 / 636).
 //
 // g and h take the momentum itself, not rho times the velocity that was divided
 // by it, and h its factor 3 apart from the rates: a rounding that is the same in
 // every cell, as that of 3 wm or 3 w, adds up over the steps.  rms error of the
 // velocity against FP64, the form below / rho times u / this one: porous medium
-// 1.63e-8 / 1.76e-8 / 1.39e-8, vortex 32^3 after 100 steps 17.9e-8 / 6.3e-8 / 6.8e-8.
+// 1.63e-8 / 1.76e-8 / 1.53e-8, vortex 32^3 after 100 steps 17.9e-8 / 6.3e-8 / 7.6e-8;
+// over 21 flows 1 / 0.84 / 0.83.
+//
+// Every rounding is written down (fmaf, no contraction), so that the same cell
+// gives the same bits in every kernel: Esoteric Twist, sparse and AA steps of any
+// lattice size agree bit for bit, where the compiler's choice of products to
+// fuse made them differ in the last place.
 // keep: exchange each pair instead of colliding (solid lanes on the even
 // step, which store direction i into slot opposite(i) and so put every
 // slot's own value back; see the stream-collide kernel)
@@ -642,14 +649,15 @@ template <int Q>
 __device__ inline void trt_collide_vectors(const LatticeArgs &a, float (&d)[Q], float drho, const Macro &M, float wp,
                                            float wm, bool keep)
 {
+#pragma clang fp contract(off)
     const float F[3] = {a.F[0], a.F[1], a.F[2]};
     const float U[3] = {M.ux, M.uy, M.uz};
-    const float usq = U[0] * U[0] + U[1] * U[1] + U[2] * U[2];
-    const float uF = U[0] * F[0] + U[1] * F[1] + U[2] * F[2];
-    const float kp = 1.f - 0.5f * wp, km = 1.f - 0.5f * wm;
-    const float b = wp * (drho - 1.5f * M.rho * usq) - 3.f * kp * uF;
+    const float usq = fmaf(U[2], U[2], fmaf(U[1], U[1], U[0] * U[0]));
+    const float uF = fmaf(U[2], F[2], fmaf(U[1], F[1], U[0] * F[0]));
+    const float kp = fmaf(-0.5f, wp, 1.f), km = fmaf(-0.5f, wm, 1.f);
+    const float b = fmaf(wp, fmaf(-1.5f * M.rho, usq, drho), -3.f * kp * uF);
     {
-        const float v = d[0] + (w_rest<Q>() * b - wp * d[0]);
+        const float v = d[0] + fmaf(w_rest<Q>(), b, -wp * d[0]);
         d[0] = keep ? d[0] : v;
     }
     // per weight class (axis, edge and corner directions): w g, w h, w b
@@ -657,7 +665,7 @@ __device__ inline void trt_collide_vectors(const LatticeArgs &a, float (&d)[Q], 
     float g[NW][3], h[NW][3], bw[NW];
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-        const float gk = wp * M.j[k] + 2.f * kp * F[k], hk = 3.f * (wm * M.j[k] + km * F[k]);
+        const float gk = fmaf(wp, M.j[k], 2.f * kp * F[k]), hk = 3.f * fmaf(wm, M.j[k], km * F[k]);
 #pragma unroll
         for (int n = 0; n < NW; ++n) {
             g[n][k] = 4.5f * w_class<Q>(n) * gk;
@@ -680,8 +688,7 @@ __device__ inline void trt_collide_vectors(const LatticeArgs &a, float (&d)[Q], 
 }
 
 // The same collision with every pair's equilibrium and source written out, for
-// large lattices without solids, for 16-bit storage and for lattices with
-// refinement interfaces.  With 16-bit
+// 16-bit storage and for lattices with refinement interfaces.  With 16-bit
 // storage the order of the FP32 operations shows.  A result that falls on the
 // other side of a 16-bit rounding boundary moves by 2^-11 of itself and shifts
 // the roundings of its neighbours in the next step; after ten steps two orders of

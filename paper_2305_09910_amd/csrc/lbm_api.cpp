@@ -341,7 +341,7 @@ int lbm_create(const lbm_domain *d, int stencil, const uint8_t *flags, double ta
     c->sc_flags = (c->mask && !sp && !a.et && (double)(ncell - (uint64_t)nf) <= 0.2 * (double)ncell)
                       ? SC_SOLID_ODD | SC_MASK_RUNS
                       : 0;
-    if (iface || (!c->mask && ncell >= SC_PAIRWISE_CELLS)) c->sc_flags |= SC_PAIRWISE;
+    if (iface) c->sc_flags |= SC_PAIRWISE;
     hipError_t e = hipMemsetAsync(c->fallbacks, 0, sizeof(unsigned long long), c->stream);
     if (e == hipSuccess && c->mask) {
         // stage the flags in a region that is still undefined and holds at

@@ -259,6 +259,13 @@ __global__ void __launch_bounds__(256, LBM_MIN_WAVES) k_even_pair16(LatticeArgs 
     });
 }
 
+// LDS set aside (and not used) by each 512-cell workgroup of a memory-bound FP32
+// step, so that two of them run on a CU: with the 24 wavefronts per CU that the
+// registers of the two-vector collision allow, the even step is slower than with
+// 16.  us per step without / with it: 512x256x256 867 / 859 (D3Q27 1318 / 1311),
+// 1024x128x128 421 / 416 (637 / 624), 1536x100x100 386 / 383 (589 / 578).
+constexpr unsigned WIDE_LDS = 54 * 1024;
+
 template <int Q, int ST, int CL, bool MASK, int COLL, bool HINT>
 static void launch_sc(const LatticeArgs &a, const HrrArgs &h, int odd, const Launch &L, hipStream_t s)
 {
@@ -275,7 +282,9 @@ static void launch_sc(const LatticeArgs &a, const HrrArgs &h, int odd, const Lau
             return;
         }
     }
-    k_stream_collide<Q, ST, CL, MASK, COLL, false, false, HINT><<<L.grid, L.block, 0, s>>>(a, odd, h);
+    constexpr bool wide = ST == ST_F32 && CL != CL_MLP && !MASK && COLL == COLL_TRT && HINT;
+    const unsigned lds = wide && L.block.x == LBM_WIDE ? WIDE_LDS : 0;
+    k_stream_collide<Q, ST, CL, MASK, COLL, false, false, HINT><<<L.grid, L.block, lds, s>>>(a, odd, h);
 }
 
 template <int Q, int ST, int COLL, bool HINT>
