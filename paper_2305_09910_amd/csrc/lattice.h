@@ -525,6 +525,11 @@ __device__ inline void noneq_flux(const LatticeArgs &a, const float (&d)[Q], flo
     flux_correction(a, pxx, pyy, pzz, pxy, pxz, pyz, drho, M, P);
 }
 
+// Whether the moments and the flux that a TRT step with closure CL takes are
+// summed by pairs (below).
+template <int ST, int CL>
+__host__ __device__ constexpr bool trt_in_pairs() { return ST == ST_F32 && CL != CL_NONE; }
+
 // Sums and differences of the opposite pairs, p_k = d_i + d_j and
 // m_k = d_i - d_j (i = 2k + 1, j = i + 1).  The even moments (density, momentum
 // flux) need only the sums, the odd ones (momentum) only the differences, and
@@ -1015,7 +1020,7 @@ template <int Q, int ST, int CL, bool PAIRWISE = false>
 __device__ inline Macro trt_cell(const LatticeArgs &a, const uint32_t *tab, float (&d)[Q], bool active, bool keep)
 {
     float drho, wp, wm;
-    if constexpr (ST == ST_F32 && CL != CL_NONE && !PAIRWISE) {
+    if constexpr (trt_in_pairs<ST, CL>() && !PAIRWISE) {
         const Pairs<Q> P(d);
         const Macro M = moments<Q>(a, P, drho);
         closure_rates<Q, CL>(a, tab, P, drho, M, active, wp, wm);

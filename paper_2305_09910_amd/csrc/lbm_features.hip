@@ -30,10 +30,16 @@ __global__ void __launch_bounds__(LBM_LB_THREADS) k_closure_features(LatticeArgs
     }
     float d[Q];
     load_state<Q, ST>(a, sp, g, m, odd, d);
-    float drho;
-    const Macro M = moments<Q>(a, d, drho);
-    float P[6], Pn[6], xf[6];
-    noneq_flux<Q>(a, d, drho, M, P);
+    float drho, P[6], Pn[6], xf[6];
+    Macro M;
+    if constexpr (trt_in_pairs<ST, CL_MLP>()) {
+        const Pairs<Q> S(d);
+        M = moments<Q>(a, S, drho);
+        noneq_flux<Q>(a, S, drho, M, P);
+    } else {
+        M = moments<Q>(a, d, drho);
+        noneq_flux<Q>(a, d, drho, M, P);
+    }
     const float excess = smag_excess(a.tau, a.cs, flux_norm(P), M.rho);
     const float ir = rcp(M.rho);
 #pragma unroll
