@@ -10,8 +10,8 @@ extern template hipError_t step_et<false>(const LatticeArgs &, int, int, int, in
 hipError_t launch_step_et(const LatticeArgs &a, int q, int st, int cl, int coll, int odd, hipStream_t s)
 {
     return (odd & SC_CACHED) && step_without_hints(a, q, st, cl, coll)
-               ? step_et<false>(a, q, st, cl, coll, odd & 1, s)
-               : step_et<true>(a, q, st, cl, coll, odd & 1, s);
+               ? step_et<false>(a, q, st, cl, coll, odd, s)
+               : step_et<true>(a, q, st, cl, coll, odd, s);
 }
 
 }  // namespace lbm

@@ -302,39 +302,59 @@ Launch lattice_launch(const LatticeArgs &a, int st, int cl, int coll, bool cache
     // Rows that 64 or 128 do not divide.  Not with the learned closure, bound
     // by its vector instructions, where idle lanes and the table per workgroup
     // cost more than seams (130: 59 in segments of 64, 66 in whole rows).
-    // Second figure: segments of 64 x 4, or 32 x 8 for multiples of 32.
+    // Measured at 26 row lengths from 70 to 1000, with 0.7 M and 6 M cells, for 25
+    // forms; quoted is the time over that of segments of 64 x 4, or 32 x 8 for
+    // multiples of 32 (geometric mean, largest).
     if (a.nx > 64 && a.nx % 128 != 0 && cl != CL_MLP) {
-        const int row64 = (a.nx + 63) / 64 * 64, half = ((a.nx + 1) / 2 + 31) / 32 * 32;
+        const bool f32 = st == ST_F32;
         auto up = [&](int w) { return (a.nx + w - 1) / w * w; };
-        auto fits = [&](int lanes) { return lanes - a.nx <= a.nx / 8; };  // few idle lanes
-        const bool heavy = a.mask || coll == COLL_MRT;
-        if (a.et && a.mask) {
-            // whole rows where the lattice stays in the cache (160: 60 / 64, 224: 78 /
-            // 88, D3Q27), else half rows, two at a time (300: 167 / 188, 444: 276 / 285)
-            if (cached && row64 <= 256) return row64 == 128 ? shape(128, 2) : shape(row64, 1);
-            if (a.nx > 200 && a.nx < LBM_WIDE && fits(2 * half)) return shape(half, 2);
-        } else if (a.nx > LBM_WIDE) {
-            // longer than a workgroup: segments of 256 or 320 cells, the one with
-            // fewer idle lanes (600: 144 / 160, 900: 131 / 141, 1000: 143 / 172)
-            if (!heavy) return up(320) < up(256) ? shape(320, 1) : shape(256, 1);
-            if (fits(up(256))) return shape(256, 1);
+        const int row64 = up(64), half = ((a.nx + 1) / 2 + 31) / 32 * 32;
+        // the widest segment that idles no more lanes than 64 x 4 does: what
+        // kernels with many registers bear (beyond 256 cells, with solids FP32
+        // 0.98, 1.05; 16-bit 0.95, 1.05, where whole or half rows are 0.98, 1.32)
+        auto widest = [&] {
+            if (f32 && up(256) == row64) return shape(256, 1);
+            return up(128) == row64 ? shape(128, 2) : shape(64, 4);
+        };
+        if (a.et && a.mask && (f32 || (row64 == 128 && !cached))) {
+            // whole rows where the lattice stays in the cache (0.97, 1.00; not
+            // multiples of 32: 160 1.04), nothing to gain elsewhere
+            if (cached && row64 == 128) return shape(128, 2);
+            if (cached && row64 <= 256 && a.nx % 32 != 0) return shape(row64, 1);
         } else if (row64 == 128) {
-            return shape(128, 2);  // 96: 20.6 / 24.0, 70: 24.7 / 30.5
+            return shape(128, 2);  // 0.91, 1.00
+        } else if (a.mask) {
+            // whole rows (FP32 0.92, 1.00 beyond the cache; in it 0.98, without
+            // multiples of 32, where 160 is 1.05; 16-bit Esoteric Twist in the
+            // cache 0.93, 1.02); 300: FP32 beyond the cache 0.98, 16-bit in it 0.99;
+            // 444: FP32 beyond it 0.95
+            if (row64 <= 256 && (f32 || (a.et && cached))) {
+                if (!f32 || !cached || a.nx % 32 != 0) return shape(row64, 1);
+            } else {
+                if (f32 != cached && row64 == 320) return shape(128, 2);
+                if (f32 && !cached && coll == COLL_TRT && row64 == 448 && 2 * half - a.nx <= a.nx / 10) return shape(half, 1);
+                return widest();
+            }
         } else if (row64 <= 256) {
-            // one workgroup per row (130: 39 / 43, 160: 31 / 39, 246 D3Q27 with
-            // solids: 158 / 174), but for small lattices with solids (222 x 63 x 55:
-            // 25.7 / 27.3, whole rows 27.7)
-            return a.mask && cached && row64 == 256 ? shape(128, 2) : shape(row64, 1);
+            return shape(row64, 1);  // one workgroup per row: 0.87, 1.05
+        } else if (a.et && !f32 && !cached) {
+            return widest();  // 0.94, 1.01; whole rows 1.02, 1.12
+        } else if (a.nx > LBM_WIDE) {
+            // longer than a workgroup: 256 cells (16-bit 0.87, 1.05), FP32 320
+            // where that idles fewer lanes (0.90, 0.98); MRT and HRR 128 x 2 (0.94,
+            // 1.06), FP32 where 256 fit as well (672 HRR 304 us, 340 with 128 x 2)
+            if (light && f32 && up(320) < up(256)) return shape(320, 1);
+            return light || a.et || (f32 && up(256) - a.nx <= a.nx / 7) ? shape(256, 1) : shape(128, 2);
+        } else if (a.et || (light && (!f32 || row64 == 320))) {
+            return shape(row64, 1);  // 0.89, 1.06
+        } else if (!f32) {
+            return widest();  // 0.96, 1.02
         } else if (row64 == 320) {
-            // 300: TRT 104 / 117, HRR 144 / 153, Esoteric Twist MRT 85 / 91; with
-            // solids (D3Q27) 241 / 245, whole rows 283; MRT 98 / 100, 102
-            return heavy && !a.et ? shape(128, 2) : shape(320, 1);
-        } else if (a.et || (st != ST_F32 && light)) {
-            return shape(row64, 1);  // 444: Esoteric Twist 102 / 110, FP16 (lines of 64 cells) 58 / 65
-        } else if (st == ST_F32 && !(a.mask && coll == COLL_MRT)) {
-            return shape(half, 1);  // 424: 101 / 108, MRT 107 / 111, HRR 134 / 140, with solids 151 / 163
-        } else if (fits(up(128))) {
-            return shape(128, 2);  // with solids (D3Q27), 376: MRT 212 / 224, FP16 151 / 154
+            return coll == COLL_HRR && cached ? shape(320, 1) : shape(128, 2);  // 0.98, 1.00
+        } else {
+            // half rows (0.91, 0.99); MRT and HRR beyond the cache where few
+            // lanes idle (400, with 48 of 448: 1.02, 424: 0.90)
+            return light || cached || 2 * half - a.nx <= a.nx / 10 ? shape(half, 1) : widest();
         }
     }
     // LBM_BLOCK threads, BX the largest power of two up to LBM_BLOCK that

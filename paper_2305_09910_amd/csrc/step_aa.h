@@ -331,7 +331,7 @@ template <int Q, int ST, bool HINT>
 static hipError_t step_q_st(const LatticeArgs &a, const HrrArgs &h, int cl, int coll, int odd, hipStream_t s)
 {
     if (!(odd & 1) && even_pair16<Q, ST, HINT>(a, cl, coll, s)) return hipGetLastError();
-    const Launch L = lattice_launch(a, ST, cl, coll, !HINT);
+    const Launch L = lattice_launch(a, ST, cl, coll, odd & SC_CACHED);
     const bool mk = a.mask != nullptr;
     if (cl == CL_MLP) {  // the learned closure runs with the TRT collision
         if (coll != COLL_TRT) return hipErrorInvalidValue;

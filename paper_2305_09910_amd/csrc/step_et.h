@@ -139,7 +139,7 @@ hipError_t step_et(const LatticeArgs &a, int q, int st, int cl, int coll, int od
 {
     if (cl == CL_MLP && coll == COLL_MRT) return hipErrorInvalidValue;
     if (coll == COLL_HRR) return hipErrorInvalidValue;  // HRR runs with the dense AA pattern only
-    const Launch L = lattice_launch(a, st, cl, coll, !HINT);
+    const Launch L = lattice_launch(a, st, cl, coll, odd & SC_CACHED);
     const bool mk = a.mask != nullptr;
     return dispatch(q, st, [&](auto Qc, auto STc) {
         constexpr int Q = decltype(Qc)::value, ST = decltype(STc)::value;
