@@ -259,12 +259,14 @@ __global__ void __launch_bounds__(256, LBM_MIN_WAVES) k_even_pair16(LatticeArgs 
     });
 }
 
-// LDS set aside (and not used) by each 512-cell workgroup of a memory-bound FP32
-// step, so that two of them run on a CU: with the 24 wavefronts per CU that the
-// registers of the two-vector collision allow, the even step is slower than with
-// 16.  us per step without / with it: 512x256x256 867 / 859 (D3Q27 1318 / 1311),
-// 1024x128x128 421 / 416 (637 / 624), 1536x100x100 386 / 383 (589 / 578).
-constexpr unsigned WIDE_LDS = 54 * 1024;
+// LDS to be set aside (and not used) by each workgroup so that at most `waves`
+// wavefronts run on a CU: the least that keeps one workgroup more from fitting
+// the 160 KB.
+inline unsigned lds_for_waves(const Launch &L, unsigned waves)
+{
+    const unsigned per = (L.block.x * L.block.y + 63) / 64, groups = waves / per;
+    return 160 * 1024 / (groups + 1) + 1280;
+}
 
 template <int Q, int ST, int CL, bool MASK, int COLL, bool HINT>
 static void launch_sc(const LatticeArgs &a, const HrrArgs &h, int odd, const Launch &L, hipStream_t s)
@@ -282,8 +284,16 @@ static void launch_sc(const LatticeArgs &a, const HrrArgs &h, int odd, const Lau
             return;
         }
     }
-    constexpr bool wide = ST == ST_F32 && CL != CL_MLP && !MASK && COLL == COLL_TRT && HINT;
-    const unsigned lds = wide && L.block.x == LBM_WIDE ? WIDE_LDS : 0;
+    // The registers of the two-vector collision allow 24 wavefronts per CU; beyond
+    // the cache the steps run better with fewer, as the pairwise form had them.  us
+    // per step without / with the limit: 512-cell rows 512x256x256 867 / 859, D3Q27
+    // 1318 / 1311, 1024x128x128 421 / 416, D3Q27 637 / 624; with solids (D3Q19,
+    // 20 instead of 24) 90x299x298 293 / 280, 246x181x180 256 / 246, 512x125x125 239 / 240.
+    unsigned lds = 0;
+    if constexpr (ST == ST_F32 && CL != CL_MLP && COLL == COLL_TRT && HINT) {
+        if (MASK && Q == 19 && CL == CL_NONE) lds = lds_for_waves(L, 20);
+        if (!MASK && L.block.x == LBM_WIDE) lds = lds_for_waves(L, 16);
+    }
     k_stream_collide<Q, ST, CL, MASK, COLL, false, false, HINT><<<L.grid, L.block, lds, s>>>(a, odd, h);
 }
 
