@@ -161,14 +161,18 @@ __device__ inline dim3 step_block(bool slabs)
 // 41.2, D3Q27 73.2 -> 65.5; 16-bit 61.3 -> 63.5, and beyond the cache 384^3 2376 ->
 // 2648, where one XCD's wavefronts all work in one slab of memory).  Without:
 // lattices that fit the eight L2s, unless neighbouring planes meet in one anyway
-// (48^3 6.9 -> 5.8, 32^3 4.6 -> 4.3, FP16 100x68x40 10.7 -> 9.0; 64^3, whose planes
-// are 16 workgroups, 7.6 -> 7.9); with 16 bits not for rows of 128, which share no
-// lines (128x100x60 12.7 -> 13.7), nor for Esoteric Twist (51x50x155 11.5 -> 12.0).
+// (48^3 6.9 -> 5.8, 32^3 4.6 -> 4.3; 64^3, whose planes are 16 workgroups, 7.6 ->
+// 7.9; time over that with hints, by MB of state: 4 0.86, 12 0.87, 20 0.86, 28 0.88).
+// With 16 bits and rows of up to 256 cells only up to a third of that (TRT 4 MB
+// 0.89, 8 0.98, 12 1.08, 20 1.05, 28 1.14; longer rows 16 MB 0.96, 24 1.03, MRT and
+// HRR 0.89, 0.95), not for rows of 128, which share no lines (128x100x60 12.7 ->
+// 13.7), nor for Esoteric Twist (51x50x155 11.5 -> 12.0).
 constexpr uint64_t L2_BYTES = 32ull << 20;
 inline bool step_in_slabs(const LatticeArgs &a, int q, int st, dim3 grid)
 {
     if (a.mask) return st == ST_F32;
-    if (cells(a) * q * (st == ST_F32 ? 4 : 2) > L2_BYTES || grid.x * grid.y % 8 == 0) return false;
+    const uint64_t bytes = cells(a) * q * (st == ST_F32 ? 4 : 2);
+    if (bytes > (st == ST_F32 || a.nx > 256 ? L2_BYTES : L2_BYTES / 3) || grid.x * grid.y % 8 == 0) return false;
     return st == ST_F32 || (a.nx % 128 != 0 && !a.et);
 }
 
