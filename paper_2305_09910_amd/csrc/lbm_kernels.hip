@@ -302,13 +302,15 @@ Launch lattice_launch(const LatticeArgs &a, int st, int cl, int coll, bool cache
     // Rows that 64 or 128 do not divide.  Not with the learned closure, bound
     // by its vector instructions, where idle lanes and the table per workgroup
     // cost more than seams (130: 59 in segments of 64, 66 in whole rows).
-    // Measured at 26 row lengths from 70 to 1000, with 0.7 M and 6 M cells, for 25
-    // forms; quoted is the time over that of segments of 64 x 4, or 32 x 8 for
+    // Measured at 26 row lengths from 70 to 1000, with 0.7 M and 6 M cells (16-bit
+    // 2.5 M as well), for 25 forms; quoted is the time over that of segments of 64 x 4, or 32 x 8 for
     // multiples of 32 (geometric mean, largest).
     if (a.nx > 64 && a.nx % 128 != 0 && cl != CL_MLP) {
         const bool f32 = st == ST_F32;
         auto up = [&](int w) { return (a.nx + w - 1) / w * w; };
         const int row64 = up(64), half = ((a.nx + 1) / 2 + 31) / 32 * 32;
+        // 16-bit lattices that are no larger than the L2s prefer other shapes
+        const bool small = cells(a) < (1u << 20);
         // the widest segment that idles no more lanes than 64 x 4 does: what
         // kernels with many registers bear (beyond 256 cells, with solids FP32
         // 0.98, 1.05; 16-bit 0.95, 1.05, where whole or half rows are 0.98, 1.32)
@@ -326,19 +328,21 @@ Launch lattice_launch(const LatticeArgs &a, int st, int cl, int coll, bool cache
         } else if (a.mask) {
             // whole rows (FP32 0.92, 1.00 beyond the cache; in it 0.98, without
             // multiples of 32, where 160 is 1.05; 16-bit Esoteric Twist in the
-            // cache 0.93, 1.02); 300: FP32 beyond the cache 0.98, 16-bit in it 0.99;
-            // 444: FP32 beyond it 0.95
+            // cache 0.91, 1.02); 300: FP32 beyond the cache 0.98, 16-bit Esoteric
+            // Twist in it 0.97 (AA 1.02), its half rows beyond 320 cells 0.88; 444:
+            // FP32 beyond the cache 0.95
             if (row64 <= 256 && (f32 || (a.et && cached))) {
                 if (!f32 || !cached || a.nx % 32 != 0) return shape(row64, 1);
             } else {
-                if (f32 != cached && row64 == 320) return shape(128, 2);
+                if (row64 == 320 && (f32 ? !cached : cached && a.et)) return shape(128, 2);
+                if (!f32 && cached && a.et && row64 > 320 && a.nx < LBM_WIDE) return shape(half, 1);
                 if (f32 && !cached && coll == COLL_TRT && row64 == 448 && 2 * half - a.nx <= a.nx / 10) return shape(half, 1);
                 return widest();
             }
         } else if (row64 <= 256) {
             return shape(row64, 1);  // one workgroup per row: 0.87, 1.05
-        } else if (a.et && !f32 && !cached) {
-            return widest();  // 0.94, 1.01; whole rows 1.02, 1.12
+        } else if (a.et && !f32 && (!cached || (coll == COLL_MRT && !small))) {
+            return widest();  // 0.95, 1.01; whole rows 1.03, 1.16
         } else if (a.nx > LBM_WIDE) {
             // longer than a workgroup: 256 cells (16-bit 0.87, 1.05), FP32 320
             // where that idles fewer lanes (0.90, 0.98); MRT and HRR 128 x 2 (0.94,
@@ -348,7 +352,9 @@ Launch lattice_launch(const LatticeArgs &a, int st, int cl, int coll, bool cache
         } else if (a.et || (light && (!f32 || row64 == 320))) {
             return shape(row64, 1);  // 0.89, 1.06
         } else if (!f32) {
-            return widest();  // 0.96, 1.02
+            // 300: 0.94 to 0.99, small 1.04; the others 0.93, 1.02
+            if (row64 == 320 && !small) return coll == COLL_HRR ? shape(320, 1) : shape(128, 2);
+            return widest();
         } else if (row64 == 320) {
             return coll == COLL_HRR && cached ? shape(320, 1) : shape(128, 2);  // 0.98, 1.00
         } else {
