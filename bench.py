@@ -20,7 +20,10 @@ Esoteric Twist and sparse addressing) as `forms`, the measured device copy
 bandwidth, the paper's own CPU figures as context, and the FP64 oracle timed
 on the host cores (`cpu_baseline`).  The same oracle runs, on stated smaller
 copies of each workload, give the velocity L2 error of every form against
-FP64 (`velocity_l2_vs_oracle`).
+FP64 (`velocity_l2_vs_oracle`).  The copies fit the last-level cache and so run
+the compilation of the steps without streaming hints, where the forms that are
+timed run the other one; a cell's arithmetic is the same in both, bit for bit
+(tests/test_gpu_beyond_cache.py).
 """
 from __future__ import annotations
 

@@ -117,8 +117,9 @@ enum { LBM_COLL_TRT = 0, LBM_COLL_MRT = 1, LBM_COLL_HRR = 2 };
  *     each fluid cell (4 bytes each) serves the odd steps.  The population
  *     store and the table are sized by the fluid cells (see
  *     lbm_workspace_bytes_flags).
- * All give the same populations up to FP32 rounding order (the same
- * arithmetic runs on the same values). */
+ * All give the same populations up to FP32 rounding order; with FP32 storage
+ * and the TRT collision bit for bit, at any lattice size (the levels of a
+ * refinement take another order of operations). */
 enum { LBM_STREAM_AA = 0, LBM_STREAM_ET = 1, LBM_STREAM_AA_SPARSE = 2 };
 
 typedef struct lbm_ctx lbm_ctx;
@@ -220,8 +221,13 @@ int lbm_get_pdfs(lbm_ctx *ctx, double *f_dev);
 int lbm_gather_pdfs(lbm_ctx *ctx, const int64_t *cells_dev, int64_t n, double *out_dev);
 
 /* Advance n >= 0 time steps (Eq. (1) then Eq. (2) per step, fused in one
- * kernel per step).  Asynchronous.  LBM_EINVAL for n < 0, LBM_ESTATE when
- * the MLP closure has no weights, LBM_EDEVICE when a launch fails. */
+ * kernel per step).  The result does not depend on how the steps are split
+ * into calls; the speed may: a lattice that fits the 256 MB last-level cache
+ * (up to 224 MB, in calls of fewer than four steps 112 MB, since other
+ * lattices may then step in between) is kept there from step to step, which
+ * is slower when several lattices stepped in turn overrun it all the same.
+ * Asynchronous.  LBM_EINVAL for n < 0, LBM_ESTATE when the MLP closure has no
+ * weights, LBM_EDEVICE when a launch fails. */
 int lbm_step(lbm_ctx *ctx, int64_t n);
 
 /* Steps (applications of Eq. (1)-(2)) taken since the last init/set/load;
@@ -275,7 +281,7 @@ int lbm_set_closure_weights(lbm_ctx *ctx, const float *params, size_t n);
 int lbm_closure_fallbacks(lbm_ctx *ctx, int64_t *count);
 
 /* The learned closure's six inputs of every cell, from the current state,
- * as the fused closure computes them before its network (the subgrid model
+ * bit for bit as the fused closure gives them to its network (the subgrid model
  * of the Section 5.1 LES channel): tr P, |dev P|, cbrt det dev P of
  * P = P_c / rho, rho - 1, tau_s - tau (Smagorinsky with cs_smag) and tau,
  * where P_c is the non-equilibrium momentum flux with its forcing

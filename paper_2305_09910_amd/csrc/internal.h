@@ -23,8 +23,8 @@ constexpr int SC_MASK_RUNS = 4;
 // trt_collide_vectors: lattices with refinement interfaces
 constexpr int SC_PAIRWISE = 8;
 // SC_CACHED (every scheme): the lattices that step together fit the 256 MB
-// last-level cache, so the streaming hints, which keep lines out of it, are off
-// (dense lattices: see step_without_hints).
+// last-level cache (short calls count them twice), so the streaming hints, which
+// keep lines out of it, are off (dense lattices: see step_without_hints).
 // us per step without and with hints: 32^3 4.3 / 4.5, 100^3 28.4 / 31.8 (D3Q27
 // with solids 58.3 / 59.9, learned closure 40.4 / 43.6), 128^3 47.4 / 49.3 (HRR,
 // 214 MB with its velocities: 61.8 / 66.7), 144^3 (227 MB) 71.8 / 74.4, 160^3 in

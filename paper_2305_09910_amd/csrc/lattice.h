@@ -1051,7 +1051,9 @@ __device__ inline Macro trt_cell(const LatticeArgs &a, const uint32_t *tab, floa
 // row addresses in scalar registers; staged before the loads, every workgroup
 // waited twice).
 struct MlpTable {
+    // every launch with the learned closure has 256 or 512 threads
     static constexpr int VECS = TAB_WORDS * 64 / 4, HELD = 4;
+    static_assert(HELD * 256 >= VECS, "the table does not fit the threads' registers");
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     u32x4 v[HELD];
     __device__ static int tid() { return threadIdx.y * blockDim.x + threadIdx.x; }
@@ -1065,7 +1067,7 @@ struct MlpTable {
             if (k < VECS) v[j] = T[k];
         }
     }
-    __device__ void put(const LatticeArgs &a, uint32_t *lds)
+    __device__ void put(uint32_t *lds)
     {
         u32x4 *L = (u32x4 *)lds;
 #pragma unroll
@@ -1073,8 +1075,6 @@ struct MlpTable {
             const int k = tid() + j * nthr();
             if (k < VECS) L[k] = v[j];
         }
-        // workgroups of fewer than VECS / HELD threads
-        for (int k = tid() + HELD * nthr(); k < VECS; k += nthr()) L[k] = ((const u32x4 *)a.mlp_tab)[k];
     }
 };
 

@@ -1,7 +1,7 @@
 // lbm_features.hip -- the learned closure's six inputs of every cell of a
 // lattice, from its current state (the subgrid model of the Section 5.1 LES
-// channel).  They are computed as the fused stream-collide kernel
-// computes them before it runs the network: the non-equilibrium momentum
+// channel).  They are computed exactly as the fused stream-collide
+// kernel computes them before it runs the network: the non-equilibrium momentum
 // flux P_c of the canonical populations (with the forcing correction), the
 // Smagorinsky excess tau_s - tau from |P_c|, and the invariants of P_c / rho.
 // Training data taken from a coarse lattice's own populations therefore has

@@ -185,7 +185,7 @@ __device__ inline double wave_sum(double v)
     return v;
 }
 
-// Sum of v over the workgroup's threads of one component: lanes, then
+// Sums over the workgroup's threads of acc, component by component: lanes, then
 // wavefronts in order.  red: one row of components per wavefront.
 template <int WAVES>
 __device__ inline void block_sums(const double (&acc)[5], double (*red)[5], double *out)

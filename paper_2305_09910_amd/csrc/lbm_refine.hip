@@ -157,9 +157,9 @@ hipError_t launch_refine_exchange(const RefineLink *links, int count, int q, int
         p[k] = {refine_row(*l.coarse, l.above ? l.coarse->ny - 1 : 0), refine_row(*l.fine, l.above ? 0 : l.fine->ny - 1),
                 l.acc, l.above};
     }
-    // one launch where both links have the same sizes and storage formats
-    const bool both = count == 2 && links[0].sc == links[1].sc && links[0].sf == links[1].sf &&
-                      p[0].coarse.nx == p[1].coarse.nx && p[0].coarse.nz == p[1].coarse.nz;
+    // one launch where both links have the same storage formats (two links are of
+    // one depth, whose levels have the same nx and nz)
+    const bool both = count == 2 && links[0].sc == links[1].sc && links[0].sf == links[1].sf;
     for (int k = 0; k < (both ? 1 : count); ++k) {
         const dim3 grid((unsigned)((p[k].coarse.nx + kRefineThreads - 1) / kRefineThreads), (unsigned)p[k].coarse.nz,
                         both ? 2 : 1);

@@ -84,7 +84,7 @@ __global__ void __launch_bounds__(256) k_stream_collide_sparse(LatticeArgs a, Sp
     });
     if constexpr (CL == CL_MLP) {
         __shared__ __align__(16) uint32_t tab_lds[TAB_WORDS * 64];
-        table.put(a, tab_lds);
+        table.put(tab_lds);
         __syncthreads();
         tab = tab_lds;
     }
@@ -161,9 +161,12 @@ hipError_t launch_build_sparse_table(const LatticeArgs &a, const SparseArgs &sp,
 // direction are written by the wavefronts of several rows and by the cells whose
 // links are cut; they leave the 4 MB L2 whole only while the chunks in flight fit
 // it (32 CUs hold 10 MB of populations and table with eight workgroups each).
-// us per step on the porous medium (256^3, 70% solid): 171.4 -> 165.5 D3Q19, 270 ->
-// 263 D3Q27; 16-bit populations fit already and lose what the wavefronts hid
-// (105 -> 113).
+// us per step on the porous medium (70% solid), without / with: 256^3 D3Q19 174.1 /
+// 173.4 D3Q27 270.4 / 268.3, 200^3 82.2 / 77.2 and 119.3 /
+// 110.9, 96^3 13.0 / 12.3; in the last-level cache 160^3 37.2 / 38.5, D3Q27 62.1 /
+// 57.5, 128^3 20.7 / 21.4.  Smagorinsky alike; MRT 96^3 15.2 / 13.7, 128^3 22.3 /
+// 23.9, 200^3 85.2 / 82.5, 256^3 182.7 / 185.8.  16-bit populations fit already and
+// lose what the wavefronts hid (105 -> 113).
 constexpr unsigned ODD_LDS_F32 = 52 * 1024;
 
 template <int Q, int ST, int COLL, bool HINT>

@@ -132,7 +132,7 @@ __device__ inline float sum_halves(float s0, float s1)
 // Standardised inputs of this lane and the B operands of layer 1 for the
 // two sample blocks: block b holds samples 32b .. 32b+31 as columns; lane l
 // supplies inputs 4(l/32) .. 4(l/32)+3 (inputs 6 and 7 are zero padding).
-__device__ inline void layer1_operands(const float *__restrict__ P, const float (&x)[6], int lane, float (&z)[6],
+__device__ inline void layer1_operands(const float *__restrict__ P, const float (&x)[6], float (&z)[6],
                                        bf16x4 &b0, bf16x4 &b1)
 {
 #pragma unroll
@@ -270,7 +270,7 @@ __device__ inline float mlp_forward_wave(const float *__restrict__ P, const floa
                                          f32x16 &h1_0, f32x16 &h1_1, f32x16 &h2_0, f32x16 &h2_1)
 {
     bf16x4 b0, b1;
-    layer1_operands(P, x, lane, z, b0, b1);
+    layer1_operands(P, x, z, b0, b1);
     const bf16x4 a1 = layer1_weights(P, lane);
     const f32x16 c1 = bias16(P, P_B1, lane);
     h1_0 = mfma32(a1, b0, c1);

@@ -77,7 +77,7 @@ __global__ void __launch_bounds__(LBM_LB_THREADS, LBM_MIN_WAVES) k_stream_collid
     });
     if constexpr (CL == CL_MLP) {
         __shared__ __align__(16) uint32_t tab_lds[TAB_WORDS * 64];
-        table.put(a, tab_lds);
+        table.put(tab_lds);
         __syncthreads();
         tab = tab_lds;
     }
