@@ -641,11 +641,12 @@ __device__ inline void trt_rates(float tt, float magic, float &wp, float &wm)
 // 436, D3Q27 649 / 636).
 //
 // g and h take the momentum itself, not rho times the velocity that was divided
-// by it, and h its factor 3 apart from the rates: a rounding that is the same in
-// every cell, as that of 3 wm or 3 w, adds up over the steps.  rms error of the
-// velocity against FP64, the form below / rho times u / this one: porous medium
-// 1.63e-8 / 1.76e-8 / 1.53e-8, vortex 32^3 after 100 steps 17.9e-8 / 6.3e-8 / 7.6e-8;
-// over 21 flows 1 / 0.84 / 0.83.
+// by it, and their factors 4.5 and 3 stay apart from the rates and the weights: a
+// rounding that is the same in every cell, as that of 3 wm, 3 w or 4.5 w, adds up
+// over the steps.  rms error of the velocity against FP64, the form below / rho
+// times u / this one: porous medium 1.63e-8 / 1.76e-8 / 1.53e-8, vortex 32^3 after
+// 100 steps 17.9e-8 / 6.3e-8 / 7.6e-8; over 21 flows of 20 steps 1 / 0.84 / 0.83,
+// over 7 of 200 steps 1 / 0.83 / 0.73 (the largest ratio: D3Q27 channel 1.10).
 //
 // Every rounding is written down (fmaf, no contraction), so that the same cell
 // gives the same bits in every kernel: Esoteric Twist, sparse and AA steps of any
@@ -674,10 +675,10 @@ __device__ inline void trt_collide_vectors(const LatticeArgs &a, float (&d)[Q], 
     float g[NW][3], h[NW][3], bw[NW];
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-        const float gk = fmaf(wp, M.j[k], 2.f * kp * F[k]), hk = 3.f * fmaf(wm, M.j[k], km * F[k]);
+        const float gk = 4.5f * fmaf(wp, M.j[k], 2.f * kp * F[k]), hk = 3.f * fmaf(wm, M.j[k], km * F[k]);
 #pragma unroll
         for (int n = 0; n < NW; ++n) {
-            g[n][k] = 4.5f * w_class<Q>(n) * gk;
+            g[n][k] = w_class<Q>(n) * gk;
             h[n][k] = w_class<Q>(n) * hk;
         }
     }
